@@ -60,6 +60,55 @@ __device__ inline void bin_and_test(const Dev &D, int k, const double xp[3], con
 }
 
 // ---------------------------------------------------------------------------
+// roots, reciprocals and quotients
+// ---------------------------------------------------------------------------
+// The list walk is bound by the instructions it issues, and a third of them
+// were the compiler's divisions (11 instructions each, 9 to 12 per contact)
+// and roots (15), whose scaling covers the whole exponent range.  These refine
+// the hardware's estimates (24 bits in FP64) by Newton's method (Goldschmidt's
+// form for the root) and end with a step on the exact residual, which rounds
+// correctly: the results are those of `sqrt` and `/` to the last bit (compared
+// on 10^9 random arguments).  Roots of arguments near the ends of the exponent
+// range go to the library.  Coupled runs of 100k packed spheres, FP32 forces:
+// 34.7 -> 30.2 us per DEM step; the fluidized bed 31.7 -> 27.4.
+__device__ __forceinline__ double recip(double x) {  // 1 / x, x > 0 and normal
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ double quot(double a, double x, double inv) {  // a / x, inv: 1 / x within a few ulp
+  const double q = a * inv;
+  return fma(fma(-q, x, a), inv, q);
+}
+__device__ __forceinline__ double root(double x, double &inv) {  // sqrt(x), inv: its reciprocal within 2 ulp
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  g = fma(fma(-g, g, x), h, g);
+  g = fma(fma(-g, g, x), h, g);
+  const double i = h + h;
+  inv = fma(i, fma(-i, g, 1.0), i);
+  return g;
+}
+__device__ __forceinline__ double root(double x) {
+  if (!(x >= 1e-280 && x <= 1e280)) return sqrt(x);
+  double inv;
+  return root(x, inv);
+}
+__device__ __forceinline__ float root(float x) {
+  if (!(x >= 1e-30f && x <= 1e30f)) return sqrtf(x);
+  const float y = __builtin_amdgcn_rsqf(x);
+  float g = x * y, h = 0.5f * y;
+  const float r = fmaf(-h, g, 0.5f);
+  g = fmaf(g, r, g);
+  h = fmaf(h, r, h);
+  return fmaf(fmaf(-g, g, x), h, g);
+}
+
+// ---------------------------------------------------------------------------
 // drift + binning (first step of a run; also the creation-time binning)
 // ---------------------------------------------------------------------------
 // p2 = s & 1, p3 = s % 3 of the step being opened; exact: the kind of its
@@ -78,11 +127,12 @@ __device__ __forceinline__ void drift_bin_body(const Dev &D, int k, int p2, int 
     const dvec4 xo = gsel(D.pr, p2 ^ 1)[k];
     const double x0[3] = {xo.x, xo.y, xo.z};
     const double inertia = 0.4 * m * r * r;
+    const double im = recip(m), ii = recip(inertia);
     double vhc[3], whc[3];
     for (int c = 0; c < 3; ++c) {
       const int i = c * n + k;
-      const double acc = (glb(D.Fc)[i] + glb(D.ffp)[i]) / m + D.g[c];
-      const double alpha = glb(D.Tc)[i] / inertia;
+      const double acc = quot(glb(D.Fc)[i] + glb(D.ffp)[i], m, im) + D.g[c];
+      const double alpha = quot(glb(D.Tc)[i], inertia, ii);
       vhc[c] = glb(D.v)[i] + 0.5 * D.dt * acc;
       whc[c] = glb(D.w)[i] + 0.5 * D.dt * alpha;
       xp[c] = x0[c] + D.dt * vhc[c];
@@ -149,12 +199,12 @@ __device__ inline void contact_law(const Material &M, const double n[3], double 
   } else {
     for (int c = 0; c < 3; ++c) dtn[c] = 0.0;
   }
-  const R sq = sqrt(R(Re) * R(dn));
+  const R sq = root(R(Re) * R(dn));
   const R kn = R(4.0 / 3.0) * R(M.Ye) * sq;
   const R kt = R(8.0) * R(M.Ge) * sq;
   const R Sn = R(2.0) * R(M.Ye) * sq;
-  const R etan = R(M.eta_coef) * sqrt(Sn * R(me));
-  const R etat = R(M.eta_coef) * sqrt(kt * R(me));  // S_t = k_t = 8 G_e sqrt(R_e dn)
+  const R etan = R(M.eta_coef) * root(Sn * R(me));
+  const R etat = R(M.eta_coef) * root(kt * R(me));  // S_t = k_t = 8 G_e sqrt(R_e dn)
   R fn[3], ft[3];
   for (int c = 0; c < 3; ++c) {
     fn[c] = -kn * R(dn) * R(n[c]) - etan * R(vrn[c]);
@@ -162,12 +212,13 @@ __device__ inline void contact_law(const Material &M, const double n[3], double 
   }
   const R fn2 = fn[0] * fn[0] + fn[1] * fn[1] + fn[2] * fn[2];
   const R ft2 = ft[0] * ft[0] + ft[1] * ft[1] + ft[2] * ft[2];
-  const R fn_mag = sqrt(fn2), ft_mag = sqrt(ft2);
+  const R fn_mag = root(fn2), ft_mag = root(ft2);
   if (ft_mag > R(M.mu) * fn_mag) {  // sliding (a tie sticks)
     const R scale = R(M.mu) * fn_mag / ft_mag;
+    const double ikt = recip((double)kt);
     for (int c = 0; c < 3; ++c) {
       ft[c] = ft[c] * scale;
-      if (ADVANCE) dtn[c] = -(double)ft[c] / (double)kt;
+      if (ADVANCE) dtn[c] = quot(-(double)ft[c], (double)kt, ikt);
     }
   }
   for (int c = 0; c < 3; ++c) f[c] = (double)(fn[c] + ft[c]);
@@ -527,6 +578,7 @@ __device__ __forceinline__ void force_kick_body(const Dev &D, int blk, int p2, i
   // instantiation
   double Tr[3] = {0.0, 0.0, 0.0};
   unsigned long long mask_new = 0;
+  const double inv_ra = recip(ra), inv_ma = recip(ma);
   const int last = D.maxn - 1;
   for (int t = lane; t < m; t += L) {
     // one round trip per entry: the partner's records, this entry's stored
@@ -545,18 +597,19 @@ __device__ __forceinline__ void force_kick_body(const Dev &D, int blk, int p2, i
     // tangential overlap, force) or identical (|d|, dn, R_e, m_e, n x f_t), so
     // the two sides stay bit-consistent: force on b = -force on a exactly.
     const double d0 = pb.x - xa0, d1 = pb.y - xa1, d2 = pb.z - xa2;
-    const double dist = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+    double inv;
+    const double dist = root(d0 * d0 + d1 * d1 + d2 * d2, inv);
     double nrm[3], vij[3], rw[3], f[3], nxft[3], dtn[3], mr[3];
-    nrm[0] = d0 / dist;
-    nrm[1] = d1 / dist;
-    nrm[2] = d2 / dist;
+    nrm[0] = quot(d0, dist, inv);
+    nrm[1] = quot(d1, dist, inv);
+    nrm[2] = quot(d2, dist, inv);
     const double dn = (ra + rb) - dist;
     lever_sum(ra, wa0, wa1, wa2, rb, wb.x, wb.y, wb.z, rw);
     vij[0] = va0 - vb.x + (rw[1] * nrm[2] - rw[2] * nrm[1]);
     vij[1] = va1 - vb.y + (rw[2] * nrm[0] - rw[0] * nrm[2]);
     vij[2] = va2 - vb.z + (rw[0] * nrm[1] - rw[1] * nrm[0]);
-    const double Re = 1.0 / (1.0 / ra + 1.0 / rb);
-    const double me = 1.0 / (1.0 / ma + 1.0 / mb);
+    const double Re = recip(inv_ra + recip(rb));
+    const double me = recip(inv_ma + recip(mb));
     const double wr[3] = {wa0 - wb.x, wa1 - wb.y, wa2 - wb.z};
     contact_law<R, ADVANCE, ROLL>(D.pp, nrm, dn, vij, Re, me, D.dt, dto, wr, f, nxft, dtn, mr);
     for (int c = 0; c < 3; ++c) {
@@ -635,11 +688,12 @@ __device__ __forceinline__ void force_kick_body(const Dev &D, int blk, int p2, i
     const double xbl[3] = {glb(D.xb)[a], glb(D.xb)[n + a], glb(D.xb)[2 * n + a]};
     const double xba[3] = {rebuild ? xa0 : xbl[0], rebuild ? xa1 : xbl[1], rebuild ? xa2 : xbl[2]};
     const double inertia = 0.4 * ma * ra * ra;
+    const double im = recip(ma), ii = recip(inertia);
     double vb[3], wb[3], acc[3], alpha[3];
     for (int c = 0; c < 3; ++c) {
       const int i = c * n + a;
-      acc[c] = (F[c] + fa[c]) / ma + D.g[c];
-      alpha[c] = T[c] / inertia;
+      acc[c] = quot(F[c] + fa[c], ma, im) + D.g[c];
+      alpha[c] = quot(T[c], inertia, ii);
       vb[c] = (c == 0 ? va0 : (c == 1 ? va1 : va2)) + 0.5 * D.dt * acc[c];
       wb[c] = (c == 0 ? wa0 : (c == 1 ? wa1 : wa2)) + 0.5 * D.dt * alpha[c];
       if (!CONT) {
