@@ -11,7 +11,7 @@
 //                 R_i + R_j + skin, the candidates shared out over the lanes
 //                 of the particle's group and tested on their position
 //                 records; sorted by partner original ID, history carried
-//                 over by a binary search of the new list in LDS),
+//                 over from the old list),
 //                 fine search (exact overlap test over the list and the six
 //                 walls), Hertz-Mindlin contact law (Table "tab:viscoelastic",
 //                 contact-force equation) with tangential history and Coulomb
@@ -35,10 +35,13 @@
 
 namespace cfddem {
 
+// The Dev that is the first argument of the running kernel.
+__device__ __forceinline__ cDev &args_dev() { return *(cDev *)__builtin_amdgcn_kernarg_segment_ptr(); }
+
 // Binning of x into the grid of a step (counts cnt, slots sl, cells cl) and
 // the displacement test against the last broad-search positions.  In a grid
 // that is not exact, a particle in its home cell (home_k) takes no slot.
-__device__ inline void bin_and_test(const Dev &D, int k, const double xp[3], const double xbk[3], gptr<int> cnt,
+__device__ inline void bin_and_test(cDev &D, int k, const double xp[3], const double xbk[3], gptr<int> cnt,
                                     gptr<int> sl, gptr<int> cl, gptr<int> flag, bool force_flag, bool exact,
                                     int home_k, int &bits) {
   int elem, cell;
@@ -116,7 +119,7 @@ __device__ __forceinline__ float root(float x) {
 // restore) and writes the step's velocity records from the boundary
 // velocities.
 template <bool DRIFT>
-__device__ __forceinline__ void drift_bin_body(const Dev &D, int k, int p2, int p3, int force_flag, bool exact) {
+__device__ __forceinline__ void drift_bin_body(cDev &D, int k, int p2, int p3, int force_flag, bool exact) {
   if (k >= D.n) return;
   const int n = D.n;
   double xp[3];
@@ -158,7 +161,7 @@ __device__ __forceinline__ void drift_bin_body(const Dev &D, int k, int p2, int 
 
 template <bool DRIFT>
 __global__ __launch_bounds__(256) void drift_bin(Dev D, int p2, int p3, int force_flag, int exact) {
-  drift_bin_body<DRIFT>(D, blockIdx.x * 256 + threadIdx.x, p2, p3, force_flag, exact != 0);
+  drift_bin_body<DRIFT>(args_dev(), blockIdx.x * 256 + threadIdx.x, p2, p3, force_flag, exact != 0);
 }
 
 // Clear the counts of grid p3 at the cells its particles were binned into
@@ -182,8 +185,8 @@ __global__ void clear_grid(Dev D, int p3) {
 // Outputs: f = f_n + f_t, nxft = n x f_t, dtn = updated tangential overlap,
 // mr = rolling torque on the first body, -mu_r R_e |f_n| wr/|wr| (zero when
 // mu_r = 0 or wr = 0; Eq. "angular_momentum" names it without a form).
-template <typename R, bool ADVANCE, bool ROLL>
-__device__ inline void contact_law(const Material &M, const double n[3], double dn,
+template <typename R, bool ADVANCE, bool ROLL, typename Mat>
+__device__ inline void contact_law(const Mat &M, const double n[3], double dn,
                                    const double vij[3], double Re, double me, double dt,
                                    const double dto[3], const double wr[3], double f[3],
                                    double nxft[3], double dtn[3], double mr[3]) {
@@ -284,30 +287,42 @@ __device__ inline void wave_publish() {
 }
 
 // Broad search of particle a by the L lanes of its group over the 27-cell
-// stencil of grid p3 / slot buffer p2.  Plane by plane, the nine cell counts
-// are loaded together, and the plane's candidates are dealt out to the lanes
-// four at a time: their slot entries in one round trip, their position
-// records and original IDs in a second, then the exact test
-// |x_b - x_a| < R_a + R_b + skin; the lanes then insert their passing
-// candidates into the group's LDS list, sorted by partner original ID, one
-// lane after the other.  Returns the list length, the same on every lane of
-// the group.
+// stencil of grid p3 / slot buffer p2.  Each lane takes every L-th of the
+// stencil's nine rows of three cells along x: the cells' counts in one round
+// trip, then the row's candidates four at a time in flight, each tested
+// exactly, |x_b - x_a| < R_a + R_b + skin; the indices of the passing ones go
+// into the group's part of LDS through a counter there.  Returns the list
+// length, the same on every lane of the group; the list is in no order (the
+// caller ranks it).
 // When the grid is not exact, a cell's candidates are first its home range
-// (particles sorted into it at the last re-sort, whether or not they are
-// still there: the exact test decides) and then its slots (particles away
-// from their home cell).  A particle within the cut-off lies in the stencil,
-// so every such pair is found; one listed both in its home range and in a
-// slot is inserted once.
+// (particles sorted into it at the last re-sort, without those that have left
+// it) and then its slots (particles away from their home cell).
+// What bounds it is the serial chain of a wavefront, so few instructions per
+// candidate count: a row's candidates are numbered over three cells, where
+// numbering a plane's over nine took a chain of selects for each, and inserting
+// each partner into a list kept sorted by ID, one lane after the other, had
+// been most of the search (a step with one: 54 to 27 us on 1,000 particles in
+// FP64, 90 to 57 us on 100k in FP32).
+// Tried and slower: candidates staged in LDS for a whole wavefront or a block
+// of four, found through a table of the distinct stencil cells or a box of
+// cells (95 to 350 us on 100k beds; with registers and LDS that the steps
+// without a search then lacked).
 template <int L>
-__device__ inline int broad_search(const Dev &D, int a, int lane, int p2, int p3, bool exact, double xa0,
-                                   double xa1, double xa2, double ra, unsigned long long *my_list, int &bits) {
+__device__ inline int broad_search(cDev &D, int a, int lane, int p2, int p3, bool exact, double xa0, double xa1,
+                                   double xa2, double ra, unsigned long long *my_list, int *my_len, int &bits) {
   constexpr int kGroups = kForceBlock / L;
-  const Grid &G = D.grid;
-  const int ca = gsel(D.cell, p3)[a];
-  const int el = ca / G.kk, sub = ca - el * G.kk;
-  const int g0 = (el % G.n_el[0]) * G.k[0] + sub % G.k[0];
-  const int g1 = ((el / G.n_el[0]) % G.n_el[1]) * G.k[1] + (sub / G.k[0]) % G.k[1];
-  const int g2 = (el / (G.n_el[0] * G.n_el[1])) * G.k[2] + sub / (G.k[0] * G.k[1]);
+  auto &G = D.grid;
+  const gptr<const int> cell = gsel(D.cell, p3);
+  int g0, g1, g2;  // the particle's cell
+  {
+    const int ca = cell[a];
+    const int el = ca / G.kk, sub = ca - el * G.kk;
+    const int ey = el / G.n_el[0], sy = sub / G.k[0];
+    g0 = (el - ey * G.n_el[0]) * G.k[0] + (sub - sy * G.k[0]);
+    const int ez = ey / G.n_el[1], sz = sy / G.k[1];
+    g1 = (ey - ez * G.n_el[1]) * G.k[1] + (sy - sz * G.k[1]);
+    g2 = ez * G.k[2] + sz;
+  }
   // the index of a stencil cell is a sum of one term per axis (element part
   // plus sub-cell part); -1 marks a term outside the grid
   int tx[3], ty[3], tz[3];
@@ -325,100 +340,93 @@ __device__ inline int broad_search(const Dev &D, int a, int lane, int p2, int p3
   const gptr<const int> hbase = glb(D.base), hstart = glb(D.start);
   const gptr<const dvec4> P = gsel(D.pr, p2);
   const double rsk = ra + D.skin;
-  constexpr int kCand = 4;
-  const int first_lane = (threadIdx.x & 63) & ~(L - 1);
-  int m = 0;
+  constexpr int kRow = 4;  // candidates in flight
+  if (lane == 0) *my_len = 0;
+  wave_publish();
+  // tests kRow candidates (b: index, own: whether it belongs to the cell it was listed in)
+  auto test = [&](const int (&b)[kRow], const bool (&on)[kRow], const int (&home)[kRow]) {
+    dvec4 pb[kRow];
+    int cb[kRow];
 #pragma unroll
-  for (int dz = 0; dz < 3; ++dz) {
-    // the plane's candidates are numbered 0 .. tot-1 across its nine cells;
-    // those of cell j are pf[j] .. hl[j]-1 (home range: particle q + ho[j])
-    // and hl[j] .. pf[j+1]-1 (slot q - hl[j] of cell cc[j])
-    int cc[9], pf[10], hl[9], ho[9];
-    pf[0] = 0;
-#pragma unroll
-    for (int j = 0; j < 9; ++j) {
-      const int z = tz[dz], y = ty[j / 3], x = tx[j % 3];
-      const bool in = z >= 0 && y >= 0 && x >= 0;
-      cc[j] = in ? z + y + x : 0;
-      const int cj = cnt[cc[j]];
-      const bool imp = in && !exact;
-      const int bj = imp ? hbase[cc[j]] : 0;
-      const int sj = imp ? hstart[cc[j]] : 0;
-      hl[j] = pf[j] + bj;
-      ho[j] = sj - pf[j];
-      pf[j + 1] = hl[j] + (in ? min(cj, D.cap) : 0);
+    for (int j = 0; j < kRow; ++j) {
+      const int i = on[j] ? b[j] : a;
+      pb[j] = P[i];
+      cb[j] = cell[i];
     }
-    const int tot = pf[9];
+    __asm__ __volatile__("" ::: "memory");  // all in flight before any is tested
+    unsigned hit = 0;
+#pragma unroll
+    for (int j = 0; j < kRow; ++j) {
+      const double d0 = pb[j].x - xa0, d1 = pb[j].y - xa1, d2 = pb[j].z - xa2;
+      const double cut = rsk + pb[j].w;
+      const bool near = d0 * d0 + d1 * d1 + d2 * d2 < cut * cut;
+      hit |= (near & on[j] & (b[j] != a) & ((home[j] < 0) | (home[j] == cb[j]))) ? 1u << j : 0u;
+    }
+    if (hit) {
+      int at = atomicAdd(my_len, __popc(hit));
+#pragma unroll
+      for (int j = 0; j < kRow; ++j)
+        if ((hit >> j) & 1u) {
+          if (at < D.maxn) my_list[at * kGroups] = (unsigned)b[j];
+          ++at;
+        }
+    }
+  };
 #pragma unroll 1
-    for (int q0 = 0; q0 < tot; q0 += kCand * L) {
-      // round trip 1: the candidates' slot entries; round trip 2: their
-      // position records and original IDs, then the exact test
-      // |x_b - x_a| < R_a + R_b + skin
-      int bq[kCand];
-      bool ok[kCand];
+  for (int r = lane; r < 9; r += L) {
+    const int dz = r / 3, dy = r - 3 * dz;
+    const int z = dz == 0 ? tz[0] : (dz == 1 ? tz[1] : tz[2]);
+    const int y = dy == 0 ? ty[0] : (dy == 1 ? ty[1] : ty[2]);
+    if (z < 0 || y < 0) continue;
+    int c[3], ns[3], nb[3], st[3];
 #pragma unroll
-      for (int i = 0; i < kCand; ++i) {
-        const int q = q0 + lane + L * i;
-        ok[i] = q < tot;
-        // the last cell whose first candidate is at or before q holds q
-        int c = cc[0], lim = hl[0], off = ho[0];
-#pragma unroll
-        for (int j = 1; j < 9; ++j)
-          if (q >= pf[j]) {
-            c = cc[j];
-            lim = hl[j];
-            off = ho[j];
-          }
-        const bool home = q < lim;
-        const size_t at = (ok[i] && !home) ? (size_t)c * D.cap + (q - lim) : 0;
-        bq[i] = home ? q + off : slot[at];
-        ok[i] = ok[i] && bq[i] != a;
-      }
-      // every candidate's loads are issued before any is tested: a test
-      // written next to its load lets the compiler sink each load into the
-      // test's branch, which then waits for it before the next one is issued
-      unsigned oq[kCand];
-      dvec4 pbq[kCand];
-#pragma unroll
-      for (int i = 0; i < kCand; ++i) {
-        const int b = ok[i] ? bq[i] : a;
-        pbq[i] = P[b];
-        oq[i] = (unsigned)glb(D.oid)[b];
-      }
-      __asm__ __volatile__("" ::: "memory");
-#pragma unroll
-      for (int i = 0; i < kCand; ++i) {
-        const double d0 = pbq[i].x - xa0, d1 = pbq[i].y - xa1, d2 = pbq[i].z - xa2;
-        const double cut = rsk + pbq[i].w;
-        ok[i] = ok[i] & (d0 * d0 + d1 * d1 + d2 * d2 < cut * cut);
-      }
-      // insertion by partner original ID, one lane of the group after the
-      // other; the list length follows each lane's turn
-#pragma unroll
-      for (int l = 0; l < L; ++l) {
-        if (lane == l) {
-#pragma unroll
-          for (int i = 0; i < kCand; ++i) {
-            if (!ok[i]) continue;
-            const unsigned long long key = ((unsigned long long)oq[i] << 32) | (unsigned)bq[i];
-            int p = m;
-            while (p > 0 && my_list[(p - 1) * kGroups] > key) --p;
-            if (p > 0 && my_list[(p - 1) * kGroups] == key) continue;  // listed twice
-            if (m < D.maxn) {
-              for (int t = m; t > p; --t) my_list[t * kGroups] = my_list[(t - 1) * kGroups];
-              my_list[p * kGroups] = key;
-              ++m;
-            } else {
-              bits |= kErrCapacity;
-            }
-          }
-        }
-        if (L > 1) {
-          wave_publish();
-          m = __shfl(m, first_lane + l, 64);
-        }
-      }
+    for (int j = 0; j < 3; ++j) {
+      c[j] = tx[j] >= 0 ? z + y + tx[j] : 0;
+      ns[j] = cnt[c[j]];
+      nb[j] = exact ? 0 : hbase[c[j]];
+      st[j] = exact ? 0 : hstart[c[j]];
     }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      ns[j] = tx[j] >= 0 ? min(ns[j], D.cap) : 0;
+      nb[j] = tx[j] >= 0 ? nb[j] : 0;
+    }
+    const int h0 = nb[0], h1 = h0 + nb[1], h2 = h1 + nb[2];
+    const int s0 = ns[0], s1 = s0 + ns[1], s2 = s1 + ns[2];
+#pragma unroll 1
+    for (int q0 = 0; q0 < h2; q0 += kRow) {
+      int b[kRow], home[kRow];
+      bool on[kRow];
+#pragma unroll
+      for (int j = 0; j < kRow; ++j) {
+        const int q = q0 + j;
+        on[j] = q < h2;
+        b[j] = q + (q < h0 ? st[0] : (q < h1 ? st[1] - h0 : st[2] - h1));
+        home[j] = q < h0 ? c[0] : (q < h1 ? c[1] : c[2]);
+      }
+      test(b, on, home);
+    }
+#pragma unroll 1
+    for (int q0 = 0; q0 < s2; q0 += kRow) {
+      int b[kRow], home[kRow];
+      bool on[kRow];
+#pragma unroll
+      for (int j = 0; j < kRow; ++j) {
+        const int q = q0 + j;
+        on[j] = q < s2;
+        const int k = q < s0 ? c[0] : (q < s1 ? c[1] : c[2]);
+        const int i = q - (q < s0 ? 0 : (q < s1 ? s0 : s1));
+        b[j] = slot[on[j] ? (size_t)k * D.cap + i : 0];
+        home[j] = -1;
+      }
+      test(b, on, home);
+    }
+  }
+  wave_publish();
+  int m = *my_len;
+  if (m > D.maxn) {
+    bits |= kErrCapacity;
+    m = D.maxn;
   }
   return m;
 }
@@ -448,13 +456,13 @@ __device__ __forceinline__ Entry load_entry(gptr<const dvec4> P, gptr<const dvec
 // ROLL: some rolling friction coefficient is nonzero (a separate
 // instantiation, so that the kernels without it keep their registers).
 template <typename R, bool ADVANCE, bool CONT, int L, bool ROLL>
-__device__ __forceinline__ void force_kick_body(const Dev &D, int blk, int p2, int p3, const int *src, int gmode) {
+__device__ __forceinline__ void force_kick_body(cDev &D, int blk, int p2, int p3, const int *src, int gmode) {
   const int gid = blk * kForceBlock + threadIdx.x;
   const int a = gid / L;
   const int lane = gid % L;
   if (a >= D.n) return;  // whole groups leave together
   const int n = D.n;
-  const Grid &G = D.grid;
+  auto &G = D.grid;
   const int q3 = p3 == 2 ? 0 : p3 + 1;  // (s + 1) % 3
   const int r3 = p3 == 0 ? 2 : p3 - 1;  // (s - 1) % 3
   const gptr<const dvec4> P = gsel(D.pr, p2);
@@ -472,23 +480,23 @@ __device__ __forceinline__ void force_kick_body(const Dev &D, int blk, int p2, i
   const unsigned wmask_a = glb(D.wmask)[a];
   const int c_old = gsel(D.cell, r3)[a];
   const int home_a = glb(D.home)[a];
-  constexpr int kCand8 = 8;     // old list entries per lane and round trip
   int bits = 0;
   int m_new = 0;                // list length after a broad search
-  unsigned long long carried = 0;  // entries of this lane with carried history
+  unsigned long long carried = 0;  // its entries with carried history
 
-  // the group's list (maxn keys, stride kGroups) and, while the history is
-  // carried after a broad search, the old position each new entry takes its
-  // history from (maxn bytes, stride kGroups)
+  // the group's list (maxn keys, stride kGroups), its length while it is
+  // found and, while the history is carried after a broad search, the old
+  // position each new entry takes its history from (maxn bytes, stride kGroups)
   extern __shared__ unsigned long long sh_list[];
   constexpr int kGroups = kForceBlock / L;
   unsigned long long *my_list = sh_list + threadIdx.x / L;
+  int *my_len = reinterpret_cast<int *>(sh_list + (size_t)D.maxn * kGroups) + threadIdx.x / L;
   unsigned char *my_from =
-      reinterpret_cast<unsigned char *>(sh_list + (size_t)D.maxn * kGroups) + threadIdx.x / L;
+      reinterpret_cast<unsigned char *>(my_len - threadIdx.x / L + kGroups) + threadIdx.x / L;
 
   if (rebuild) {
     const int m = broad_search<L>(D, a, lane, p2, p3, (gmode & kGridCurExact) != 0, xa0, xa1, xa2, ra, my_list,
-                                  bits);
+                                  my_len, bits);
     m_new = m;
     if (lane == 0) {
       gsel(D.ln, cur)[a] = m;
@@ -496,57 +504,87 @@ __device__ __forceinline__ void force_kick_body(const Dev &D, int blk, int p2, i
       glb(D.xb)[n + a] = xa1;
       glb(D.xb)[2 * n + a] = xa2;
     }
-    // ---- tangential history of the pairs that touched at the last step:
-    //      each lane finds its share of the old touching entries in the new
-    //      (sorted) list by binary search in LDS and notes where each new
-    //      entry's history comes from; then every lane stores its own new
-    //      entries and copies their history
+    // ---- the list sorted by partner original ID, with the tangential history
+    //      of the pairs that touched at the last step: each lane finds its
+    //      share of the old touching entries in the new list and notes where
+    //      each new entry's history comes from; then it ranks its share of the
+    //      new entries, four at a time in flight, and stores them
     const int s = src ? glb(src)[a] : a;
-    const int mo = gsel(D.ln, lold)[s];
+    const int mo = ADVANCE ? gsel(D.ln, lold)[s] : 0;
     const unsigned long long mask_old = gsel(D.hmask, lold)[s];
     const gptr<const unsigned long long> olst = gsel(D.nbr, lold);
-    for (int t = lane; t < m; t += L) my_from[t * kGroups] = 0;
-    wave_publish();
-    if (ADVANCE) {
+    constexpr int kStrip = 4;
 #pragma unroll 1
-      for (int q0 = 0; q0 < mo; q0 += kCand8 * L) {
-        unsigned ok_old[kCand8];
+    for (int t0 = 0; t0 < m; t0 += kStrip * L) {
+      unsigned b[kStrip], o[kStrip];
 #pragma unroll
-        for (int i = 0; i < kCand8; ++i) {
-          const int qo = q0 + lane + L * i;
-          const bool live = qo < mo && ((mask_old >> qo) & 1ull);
-          ok_old[i] = live ? (unsigned)(olst[(size_t)qo * n + s] >> 32) : 0xffffffffu;
-        }
-#pragma unroll
-        for (int i = 0; i < kCand8; ++i) {
-          if (ok_old[i] == 0xffffffffu) continue;
-          int lo = 0, hi = m - 1;
-          while (lo <= hi) {
-            const int mid = (lo + hi) >> 1;
-            const unsigned om = (unsigned)(my_list[mid * kGroups] >> 32);
-            if (om == ok_old[i]) {
-              my_from[mid * kGroups] = (unsigned char)(q0 + lane + L * i + 1);
-              break;
-            }
-            if (om < ok_old[i])
-              lo = mid + 1;
-            else
-              hi = mid - 1;
-          }
-        }
+      for (int i = 0; i < kStrip; ++i) {
+        b[i] = (unsigned)my_list[min(t0 + lane + L * i, m - 1) * kGroups];
+        o[i] = (unsigned)glb(D.oid)[b[i]];
       }
-      wave_publish();
+#pragma unroll
+      for (int i = 0; i < kStrip; ++i) {
+        const int t = t0 + lane + L * i;
+        if (t >= m) continue;
+        my_list[t * kGroups] = ((unsigned long long)o[i] << 32) | b[i];
+        my_from[t * kGroups] = 0;
+      }
     }
+    wave_publish();
+#pragma unroll 1
+    for (int q0 = 0; q0 < mo; q0 += kStrip * L) {
+      unsigned oo[kStrip];
+      int at[kStrip];  // place of the old entry's partner in the new list, -1: none
+#pragma unroll
+      for (int i = 0; i < kStrip; ++i) {
+        oo[i] = (unsigned)(olst[(size_t)min(q0 + lane + L * i, mo - 1) * n + s] >> 32);
+        at[i] = -1;
+      }
+#pragma unroll 2
+      for (int t = 0; t < m; ++t) {
+        const unsigned o = (unsigned)(my_list[t * kGroups] >> 32);
+#pragma unroll
+        for (int i = 0; i < kStrip; ++i) at[i] = o == oo[i] ? t : at[i];
+      }
+#pragma unroll
+      for (int i = 0; i < kStrip; ++i) {
+        const int q = q0 + lane + L * i;
+        if (q < mo && ((mask_old >> q) & 1ull) && at[i] >= 0) my_from[at[i] * kGroups] = (unsigned char)(q + 1);
+      }
+    }
+    wave_publish();
     const gptr<unsigned long long> lst_new = gsel(D.nbr, cur);
-    for (int t = lane; t < m; t += L) {
-      lst_new[(size_t)t * n + a] = my_list[t * kGroups];
-      const int from = my_from[t * kGroups];
-      if (from) {
-        for (int c = 0; c < 3; ++c)
-          gsel(D.hdt, cur)[hist_at(t, n, a) + c] = gsel(D.hdt, lold)[hist_at(from - 1, n, s) + c];
-        carried |= 1ull << t;
+#pragma unroll 1
+    for (int t0 = 0; t0 < m; t0 += kStrip * L) {
+      unsigned long long key[kStrip];
+      int rank[kStrip], from[kStrip];
+      double h[kStrip][3];
+#pragma unroll
+      for (int i = 0; i < kStrip; ++i) {
+        const int t = min(t0 + lane + L * i, m - 1);
+        key[i] = my_list[t * kGroups];
+        from[i] = my_from[t * kGroups];
+        rank[i] = 0;
+        const size_t fr = hist_at(max(from[i], 1) - 1, n, s);
+        for (int c = 0; c < 3; ++c) h[i][c] = gsel(D.hdt, lold)[fr + c];
+      }
+#pragma unroll 2
+      for (int q = 0; q < m; ++q) {
+        const unsigned long long v = my_list[q * kGroups];
+#pragma unroll
+        for (int i = 0; i < kStrip; ++i) rank[i] += v < key[i] ? 1 : 0;
+      }
+#pragma unroll
+      for (int i = 0; i < kStrip; ++i) {
+        if (t0 + lane + L * i >= m) continue;
+        lst_new[(size_t)rank[i] * n + a] = key[i];
+        if (!from[i]) continue;
+        for (int c = 0; c < 3; ++c) gsel(D.hdt, cur)[hist_at(rank[i], n, a) + c] = h[i][c];
+        carried |= 1ull << rank[i];
       }
     }
+    carried = group_or<L>(carried);
+    __syncthreads();  // entries stored by the particle's other lanes
   }
   // keep the fast path's loads below the (rare) broad search, so that their
   // registers are not live across it
@@ -569,7 +607,7 @@ __device__ __forceinline__ void force_kick_body(const Dev &D, int blk, int p2, i
   const double wa0 = wa.x, wa1 = wa.y, wa2 = wa.z;
   const unsigned wold = (ADVANCE && lane == L - 1) ? wmask_a : 0u;
   const int m = rebuild ? m_new : lnv;
-  unsigned long long mask_prev = rebuild ? carried : hm;
+  const unsigned long long mask_prev = rebuild ? carried : hm;
 
   // ---- fine search and forces over this lane's list entries
   double F[3] = {0.0, 0.0, 0.0}, T[3] = {0.0, 0.0, 0.0};
@@ -662,7 +700,6 @@ __device__ __forceinline__ void force_kick_body(const Dev &D, int blk, int p2, i
   if (ROLL && (D.pp.mu_r > 0.0 || D.pw.mu_r > 0.0))
     for (int c = 0; c < 3; ++c) T[c] += group_sum<L>(Tr[c]);
   mask_new = group_or<L>(mask_new);
-  mask_prev = group_or<L>(mask_prev);
   if (lane != 0) {
     if (bits) __hip_atomic_fetch_or(glb(D.err), bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
@@ -753,18 +790,28 @@ __device__ inline int xcd_run_block(int i, int nb, int C) {
   return ((j / C) * kXcds + x) * C + j % C;
 }
 
+// Wavefronts per SIMD that the force kernels leave registers for.  Four are
+// 128 registers, which holds every FP32 variant and the plain FP64 one; with
+// rolling friction, or over a batch's table, the FP64 kernel needs up to 23
+// more.  It gets them: held in scratch memory instead they cost time on every
+// step, and a build that did so gave results that differed from run to run.
+template <typename R, bool ROLL, bool BATCH>
+constexpr int force_waves() {
+  return sizeof(R) == 8 && (ROLL || BATCH) ? 3 : 4;
+}
+
 template <typename R, bool ADVANCE, bool CONT, int L, bool ROLL>
-__global__ __launch_bounds__(kForceBlock, 4) void force_kick(Dev D, int p2, int p3, const int *src, int gmode) {
-  force_kick_body<R, ADVANCE, CONT, L, ROLL>(D, xcd_block(blockIdx.x, gridDim.x), p2, p3, src, gmode);
+__global__ __launch_bounds__(kForceBlock, (force_waves<R, ROLL, false>())) void force_kick(Dev D, int p2, int p3, const int *src, int gmode) {
+  force_kick_body<R, ADVANCE, CONT, L, ROLL>(args_dev(), xcd_block(blockIdx.x, gridDim.x), p2, p3, src, gmode);
 }
 
 // ---------------------------------------------------------------------------
 // batched kernels: one launch over every bed of a batch
 // ---------------------------------------------------------------------------
-// Dynamic LDS of the contact-force kernel: per group, maxn list keys and
-// maxn history-source bytes.
+// Dynamic LDS of the contact-force kernel: per group, maxn list keys, a
+// length and maxn history-source bytes.
 static size_t force_lds_bytes(int maxn, int L) {
-  return (sizeof(unsigned long long) + 1) * (size_t)maxn * (kForceBlock / L);
+  return ((sizeof(unsigned long long) + 1) * (size_t)maxn + sizeof(int)) * (kForceBlock / L);
 }
 
 __device__ inline void bed_of_block(const unsigned *__restrict__ map, int &bed, int &blk) {
@@ -779,7 +826,7 @@ __global__ __launch_bounds__(256) void drift_bin_batch(const Dev *__restrict__ t
                                                        const unsigned *__restrict__ map, int n) {
   int b, blk;
   bed_of_block(map, b, blk);
-  const Dev &D = tab[b];
+  cDev &D = ((cDev *)tab)[b];
   const long long s = run[b].s + 1;
   drift_bin_body<true>(D, blk * 256 + threadIdx.x, (int)(s & 1), (int)(s % 3),
                        run[b].src != nullptr, n == 1);
@@ -788,13 +835,13 @@ __global__ __launch_bounds__(256) void drift_bin_batch(const Dev *__restrict__ t
 // Step run.s + i of every bed, of a run of n steps (i = 1 applies the bed's
 // pending permutation).
 template <typename R, bool CONT, int L, bool ROLL>
-__global__ __launch_bounds__(kForceBlock, 4) void force_kick_batch(const Dev *__restrict__ tab,
+__global__ __launch_bounds__(kForceBlock, (force_waves<R, ROLL, true>())) void force_kick_batch(const Dev *__restrict__ tab,
                                                                    const BedRun *__restrict__ run,
                                                                    const unsigned *__restrict__ map,
                                                                    int i, int n) {
   const unsigned m = map[xcd_run_block(blockIdx.x, gridDim.x, kBatchXcdRun)];
   const int b = (int)(m >> kBedShift), blk = (int)(m & kBlockMask);
-  const Dev &D = tab[b];
+  cDev &D = ((cDev *)tab)[b];
   const long long s = run[b].s + i;
   force_kick_body<R, true, CONT, L, ROLL>(D, blk, (int)(s & 1), (int)(s % 3),
                                           i == 1 ? run[b].src : nullptr, grid_mode(i, n));

@@ -195,8 +195,21 @@ __device__ __forceinline__ gptr<T> glb(T *p) {
   return (gptr<T>)p;
 }
 
+// A Dev read where it stands in constant memory (a kernel's argument segment or
+// a batch table): its fields come by scalar loads where they are used, instead
+// of all of them being held in registers from the start of the kernel.
+typedef const __attribute__((address_space(4))) Dev cDev;
+
 // Buffer i of a double- or triple-buffered array, with constant indices only
 // (so that a Dev copied into registers stays in registers).
+template <typename T>
+__device__ __forceinline__ T *sel(T *const __attribute__((address_space(4))) (&a)[2], int i) {
+  return i ? a[1] : a[0];
+}
+template <typename T>
+__device__ __forceinline__ T *sel(T *const __attribute__((address_space(4))) (&a)[3], int i) {
+  return i == 0 ? a[0] : (i == 1 ? a[1] : a[2]);
+}
 template <typename T>
 __device__ __forceinline__ T *sel(T *const (&a)[2], int i) {
   return i ? a[1] : a[0];
@@ -209,6 +222,10 @@ template <typename T, int K>
 __device__ __forceinline__ gptr<T> gsel(T *const (&a)[K], int i) {
   return glb(sel(a, i));
 }
+template <typename T, int K>
+__device__ __forceinline__ gptr<T> gsel(T *const __attribute__((address_space(4))) (&a)[K], int i) {
+  return glb(sel(a, i));
+}
 
 __device__ inline int floor_clamp(double t, int n) {
   double f = floor(t);
@@ -219,7 +236,8 @@ __device__ inline int floor_clamp(double t, int n) {
 
 // Hierarchical binning, evaluated without FMA contraction so that the indices
 // are a pure function of the IEEE operations written here.
-__device__ inline void bin_point(const Grid &G, const double xp[3], int &elem, int &cell,
+template <typename GridRef>
+__device__ inline void bin_point(GridRef &G, const double xp[3], int &elem, int &cell,
                                  bool &inside) {
 #pragma clang fp contract(off)
   int e[3], s[3];

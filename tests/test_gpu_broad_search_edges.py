@@ -1,0 +1,57 @@
+"""Neighbour lists and carried histories where a broad search can go wrong:
+beds that rebuild their lists on almost every step, with list lengths that are
+no multiple of a lane's share, particles away from their home cell, unsorted
+beds, stencils cut off by every wall, and rolling friction."""
+import numpy as np
+import pytest
+
+from paper_2211_01185_amd import synth
+from tests.parity_util import TOL, compare_contacts, compare_states, gpu_bed, gpu_state, oracle_bed
+
+pytestmark = pytest.mark.gpu
+
+pytest.importorskip("torch")
+
+VARIANTS = [(p, lanes, mu_r) for p in ("fp64", "fp32") for lanes in (1, 2, 4) for mu_r in (0.0, 0.1)]
+
+
+def _moving_lattice(n_side, mu_r):
+    """Touching lattice in a box without clearance along x, in fast motion."""
+    wl = synth.lattice(n_side=n_side)
+    wl.v[:] = np.random.default_rng(3).normal(0.0, 0.3, wl.v.shape)
+    wl.x[0] -= 0.005
+    wl.dem["box_hi"][0] -= 0.01
+    wl.dem["mu_r"] = mu_r
+    return wl
+
+
+@pytest.mark.parametrize("resort_every", [5, 1000])
+@pytest.mark.parametrize("lanes", [1, 2, 4])
+def test_rebuilt_lists_against_the_oracle(lanes, resort_every):
+    wl = _moving_lattice((9, 8, 11), 0.1)
+    gb = gpu_bed(wl, "fp64", lanes=lanes, resort_every=resort_every, skin=1e-5)
+    ob, _ = oracle_bed(wl)
+    for _ in range(4):
+        gb.step(3)
+        ob.step(3)
+        # up to twelve steps: a single step's tolerance for each
+        assert compare_contacts(gb, ob, 12 * TOL["fp64"]) > 1500
+        compare_states(gb, ob, 12 * TOL["fp64"], keys=("x", "v", "w", "Fc", "Tc"))
+    assert gb.poll()[0] == 0
+
+
+@pytest.mark.parametrize("precision,lanes,mu_r", VARIANTS)
+def test_rebuilt_lists_have_the_same_bits_each_time(precision, lanes, mu_r):
+    """Enough wavefronts to fill the chip; nothing may depend on their order."""
+    wl = _moving_lattice((32, 32, 32), mu_r)
+    runs = []
+    for _ in range(2):
+        gb = gpu_bed(wl, precision, lanes=lanes, resort_every=7, skin=1e-5)
+        gb.step(20)
+        runs.append((gpu_state(gb), gb.read_contacts()))
+        assert gb.poll()[0] == 0
+    (a, ca), (b, cb) = runs
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
+    for p, q in zip(ca, cb):
+        assert np.array_equal(p, q)

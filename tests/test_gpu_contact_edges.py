@@ -23,9 +23,9 @@ def _pair(overlap, ratio, density_ratio, spin):
     wl.x[:, 1] = wl.x[:, 0] + u * (r.sum() / (1.0 + overlap))
     wl.v[:] = [[0.01, -0.02], [0.0, 0.01], [0.003, -0.001]]
     wl.w[:] = [[30.0, -10.0], [-20.0, 5.0], [4.0, 40.0]]
-    if not spin:
+    if not spin:  # at rest: the spring alone
         wl.w[:] = 0.0
-        wl.v[:] = np.outer(u, [0.01, -0.02])
+        wl.v[:] = 0.0
     return wl
 
 
