@@ -231,6 +231,7 @@ dem_status derive(const dem_params *dp, const cfd_params *cp, Sizes &S) {
     G.k[a] = (int)kd;
     G.inv_hc[a] = (double)(G.k[a] * cp->n_el[a]) / len;
     G.gc[a] = G.k[a] * cp->n_el[a];
+    G.hc[a] = G.he[a] / (double)G.k[a];
     if (G.he[a] / G.k[a] > hc_max) hc_max = G.he[a] / G.k[a];
     n_elem *= cp->n_el[a];
     ncells *= (long long)G.gc[a];
@@ -1141,6 +1142,10 @@ dem_status dem_create(const dem_params *dp, const cfd_params *cp, const double *
   D.maxn = S.maxn;
   D.skin = S.skin;
   D.trig2 = (0.499 * S.skin) * (0.499 * S.skin);
+  // the margin covers the rounding of cell faces and of the binning
+  D.reach = 0.5 * dp->d_max + S.skin;
+  for (int a = 0; a < 3; ++a)
+    D.reach += 1e-6 * S.grid.hc[a] + 1e-14 * (fabs(S.grid.lo[a]) + fabs(S.grid.hi[a]));
   D.dt = dp->dt;
   for (int a = 0; a < 3; ++a) D.g[a] = dp->gravity[a];
   D.grid = S.grid;

@@ -42,6 +42,7 @@ struct Grid {
   double he[3];      // element size
   double inv_he[3];  // n_el / (hi - lo)
   double inv_hc[3];  // (k n_el) / (hi - lo)
+  double hc[3];      // cell size
   int n_el[3];
   int k[3];
   int kk;            // k0 k1 k2: cells per element
@@ -62,6 +63,7 @@ struct Dev {
   double dt;
   double g[3];
   double skin;        // neighbour-list skin
+  double reach;       // broad search: a partner's centre is at most R_a + reach away
   double trig2;       // squared displacement that triggers a new broad search
   Material pp, pw;
   Grid grid;
