@@ -254,9 +254,11 @@ __device__ inline void lever_sum(double ra, double wa0, double wa1, double wa2, 
 // ---------------------------------------------------------------------------
 // one DEM step (plus the opening of the next one when CONT)
 // ---------------------------------------------------------------------------
-// L consecutive lanes of a wavefront share one particle: lane l walks the list
-// entries t = l, l + L, ..., lane L-1 also the walls, and the partial force
-// and torque are summed over the L lanes in a fixed butterfly order.  When a
+// A particle's list is walked in V parts (the caller's lanes), part v holding
+// the entries t = v, v + V, ..., the last part also the walls; the parts' forces
+// and torques are summed in a fixed butterfly order.  Each part is shared by S
+// lanes, which find its contacts side by side and add them up in the order of
+// t, all of them the same sum: V S = L consecutive lanes per particle.  When a
 // broad search is due the group's lanes share its candidates and build the
 // list in LDS; every lane then stores its own entries.  Lane 0 finishes the
 // step.  p2 = s & 1, p3 = s % 3.  The grid p3 / slot buffer p2 hold x_s.
@@ -264,10 +266,32 @@ __device__ inline void lever_sum(double ra, double wa0, double wa1, double wa2, 
 // src: after a re-sort, the index each particle had when its list was built
 //      (NULL otherwise).
 // gmode: kGrid* bits, the kinds of the grids of steps s, s+1 and s-1.
-template <int L>
+// Sum over the lanes 0, S, 2 S, .. of a group of L.
+template <int L, int S>
 __device__ inline double group_sum(double v) {
-  for (int off = 1; off < L; off <<= 1) v += __shfl_xor(v, off, 64);
+  for (int off = S; off < L; off <<= 1) v += __shfl_xor(v, off, 64);
   return v;
+}
+// v of the U-th of the S lanes (1, 2 or 4) sharing one part of a particle's list.
+template <int S, int U>
+__device__ __forceinline__ double share_get(double v) {
+  constexpr int kPerm = S == 2 ? (U ? 0xf5 : 0xa0) : U * 0x55;  // quad permutation
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), kPerm, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), kPerm, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+// Adds one contact's part on each of the S lanes, in their order, the same on all.
+template <int S, int U, bool ROLL>
+__device__ __forceinline__ void share_add(double ra, const double f[3], const double nxft[3], const double mr[3],
+                                          double F[3], double T[3], double Tr[3]) {
+  if constexpr (U < S) {
+    for (int c = 0; c < 3; ++c) {
+      F[c] += share_get<S, U>(f[c]);
+      T[c] += ra * share_get<S, U>(nxft[c]);
+      if (ROLL) Tr[c] += share_get<S, U>(mr[c]);
+    }
+    share_add<S, U + 1, ROLL>(ra, f, nxft, mr, F, T, Tr);
+  }
 }
 template <int L>
 __device__ inline unsigned long long group_or(unsigned long long v) {
@@ -495,8 +519,9 @@ __device__ __forceinline__ Entry load_entry(gptr<const dvec4> P, gptr<const dvec
 
 // ROLL: some rolling friction coefficient is nonzero (a separate
 // instantiation, so that the kernels without it keep their registers).
-template <typename R, bool ADVANCE, bool CONT, int L, bool ROLL>
+template <typename R, bool ADVANCE, bool CONT, int V, bool ROLL, int S>
 __device__ __forceinline__ void force_kick_body(cDev &D, int blk, int p2, int p3, const int *src, int gmode) {
+  constexpr int L = V * S;  // lanes of a particle
   const int gid = blk * kForceBlock + threadIdx.x;
   const int a = gid / L;
   const int lane = gid % L;
@@ -520,6 +545,8 @@ __device__ __forceinline__ void force_kick_body(cDev &D, int blk, int p2, int p3
   const unsigned wmask_a = glb(D.wmask)[a];
   const int c_old = gsel(D.cell, r3)[a];
   const int home_a = glb(D.home)[a];
+  const int sub = lane % S;
+  const int first = lane / S + V * sub;  // this lane's first entry; every L-th follows
   int bits = 0;
   int m_new = 0;                // list length after a broad search
   unsigned long long carried = 0;  // its entries with carried history
@@ -641,11 +668,11 @@ __device__ __forceinline__ void force_kick_body(cDev &D, int blk, int p2, int p3
   const gptr<double> hdt = gsel(D.hdt, cur);
   const unsigned long long hm = gsel(D.hmask, cur)[a];
   const int lnv = gsel(D.ln, cur)[a];
-  unsigned long long key = lst[(size_t)min(lane, D.maxn - 1) * n + a];
+  unsigned long long key = lst[(size_t)min(first, D.maxn - 1) * n + a];
   const dvec4 va = VM[a], wa = WS[a];
   const double va0 = va.x, va1 = va.y, va2 = va.z, ma = va.w;
   const double wa0 = wa.x, wa1 = wa.y, wa2 = wa.z;
-  const unsigned wold = (ADVANCE && lane == L - 1) ? wmask_a : 0u;
+  const unsigned wold = (ADVANCE && lane == L - S) ? wmask_a : 0u;
   const int m = rebuild ? m_new : lnv;
   const unsigned long long mask_prev = rebuild ? carried : hm;
 
@@ -658,7 +685,7 @@ __device__ __forceinline__ void force_kick_body(cDev &D, int blk, int p2, int p3
   unsigned long long mask_new = 0;
   const double inv_ra = recip(ra), inv_ma = recip(ma);
   const int last = D.maxn - 1;
-  for (int t = lane; t < m; t += L) {
+  for (int t = first; t - V * sub < m; t += L) {
     // one round trip per entry: the partner's records, this entry's stored
     // tangential overlap and the next entry's key (its slot clamped to the
     // list capacity; past the list's length its value is not used)
@@ -666,40 +693,45 @@ __device__ __forceinline__ void force_kick_body(cDev &D, int blk, int p2, int p3
     key = lst[(size_t)min(t + L, last) * n + a];
     const dvec4 pb = cur_e.p, vb = cur_e.v, wb = cur_e.w;
     const double rb = pb.w;
-    if (!touching(xa0, xa1, xa2, pb.x, pb.y, pb.z, ra, rb)) continue;
-    const bool had = ADVANCE && ((mask_prev >> t) & 1ull);
-    const double dto[3] = {had ? cur_e.h[0] : 0.0, had ? cur_e.h[1] : 0.0, had ? cur_e.h[2] : 0.0};
-    const double mb = vb.w;
-    // Evaluated from this particle's side.  Every quantity the partner
-    // computes from its side is the exact negation (d, n, relative velocity,
-    // tangential overlap, force) or identical (|d|, dn, R_e, m_e, n x f_t), so
-    // the two sides stay bit-consistent: force on b = -force on a exactly.
-    const double d0 = pb.x - xa0, d1 = pb.y - xa1, d2 = pb.z - xa2;
-    double inv;
-    const double dist = root(d0 * d0 + d1 * d1 + d2 * d2, inv);
-    double nrm[3], vij[3], rw[3], f[3], nxft[3], dtn[3], mr[3];
-    nrm[0] = quot(d0, dist, inv);
-    nrm[1] = quot(d1, dist, inv);
-    nrm[2] = quot(d2, dist, inv);
-    const double dn = (ra + rb) - dist;
-    lever_sum(ra, wa0, wa1, wa2, rb, wb.x, wb.y, wb.z, rw);
-    vij[0] = va0 - vb.x + (rw[1] * nrm[2] - rw[2] * nrm[1]);
-    vij[1] = va1 - vb.y + (rw[2] * nrm[0] - rw[0] * nrm[2]);
-    vij[2] = va2 - vb.z + (rw[0] * nrm[1] - rw[1] * nrm[0]);
-    const double Re = recip(inv_ra + recip(rb));
-    const double me = recip(inv_ma + recip(mb));
-    const double wr[3] = {wa0 - wb.x, wa1 - wb.y, wa2 - wb.z};
-    contact_law<R, ADVANCE, ROLL>(D.pp, nrm, dn, vij, Re, me, D.dt, dto, wr, f, nxft, dtn, mr);
-    for (int c = 0; c < 3; ++c) {
-      F[c] += f[c];
-      T[c] += ra * nxft[c];  // R_a n x f_t (n x f_t is the same from both sides)
-      if (ROLL) Tr[c] += mr[c];  // the partner's is the exact negation
-      hdt[hist_at(t, n, a) + c] = dtn[c];
+    double f[3] = {0.0, 0.0, 0.0}, nxft[3] = {0.0, 0.0, 0.0}, mr[3] = {0.0, 0.0, 0.0};
+    if ((S == 1 || t < m) && touching(xa0, xa1, xa2, pb.x, pb.y, pb.z, ra, rb)) {
+      const bool had = ADVANCE && ((mask_prev >> t) & 1ull);
+      const double dto[3] = {had ? cur_e.h[0] : 0.0, had ? cur_e.h[1] : 0.0, had ? cur_e.h[2] : 0.0};
+      const double mb = vb.w;
+      // Evaluated from this particle's side.  Every quantity the partner
+      // computes from its side is the exact negation (d, n, relative velocity,
+      // tangential overlap, force) or identical (|d|, dn, R_e, m_e, n x f_t), so
+      // the two sides stay bit-consistent: force on b = -force on a exactly.
+      const double d0 = pb.x - xa0, d1 = pb.y - xa1, d2 = pb.z - xa2;
+      double inv;
+      const double dist = root(d0 * d0 + d1 * d1 + d2 * d2, inv);
+      double nrm[3], vij[3], rw[3], dtn[3];
+      nrm[0] = quot(d0, dist, inv);
+      nrm[1] = quot(d1, dist, inv);
+      nrm[2] = quot(d2, dist, inv);
+      const double dn = (ra + rb) - dist;
+      lever_sum(ra, wa0, wa1, wa2, rb, wb.x, wb.y, wb.z, rw);
+      vij[0] = va0 - vb.x + (rw[1] * nrm[2] - rw[2] * nrm[1]);
+      vij[1] = va1 - vb.y + (rw[2] * nrm[0] - rw[0] * nrm[2]);
+      vij[2] = va2 - vb.z + (rw[0] * nrm[1] - rw[1] * nrm[0]);
+      const double Re = recip(inv_ra + recip(rb));
+      const double me = recip(inv_ma + recip(mb));
+      const double wr[3] = {wa0 - wb.x, wa1 - wb.y, wa2 - wb.z};
+      contact_law<R, ADVANCE, ROLL>(D.pp, nrm, dn, vij, Re, me, D.dt, dto, wr, f, nxft, dtn, mr);
+      for (int c = 0; c < 3; ++c) {
+        if constexpr (S == 1) {
+          F[c] += f[c];
+          T[c] += ra * nxft[c];  // R_a n x f_t (n x f_t is the same from both sides)
+          if (ROLL) Tr[c] += mr[c];  // the partner's is the exact negation
+        }
+        hdt[hist_at(t, n, a) + c] = dtn[c];
+      }
+      mask_new |= 1ull << t;
     }
-    mask_new |= 1ull << t;
+    if constexpr (S > 1) share_add<S, 0, ROLL>(ra, f, nxft, mr, F, T, Tr);
   }
   // ---- walls (last lane of the group)
-  if (lane == L - 1) {
+  if (lane == L - S) {
     unsigned wnew = 0;
     for (int wall = 0; wall < kWalls; ++wall) {
       // axis quantities by selection (no run-time index into the grid)
@@ -734,11 +766,11 @@ __device__ __forceinline__ void force_kick_body(cDev &D, int blk, int p2, int p3
     if (wnew != wold || !ADVANCE) glb(D.wmask)[a] = (unsigned char)wnew;
   }
   for (int c = 0; c < 3; ++c) {
-    F[c] = group_sum<L>(F[c]);
-    T[c] = group_sum<L>(T[c]);
+    F[c] = group_sum<L, S>(F[c]);
+    T[c] = group_sum<L, S>(T[c]);
   }
   if (ROLL && (D.pp.mu_r > 0.0 || D.pw.mu_r > 0.0))
-    for (int c = 0; c < 3; ++c) T[c] += group_sum<L>(Tr[c]);
+    for (int c = 0; c < 3; ++c) T[c] += group_sum<L, S>(Tr[c]);
   mask_new = group_or<L>(mask_new);
   if (lane != 0) {
     if (bits) __hip_atomic_fetch_or(glb(D.err), bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -840,9 +872,9 @@ constexpr int force_waves() {
   return sizeof(R) == 8 && (ROLL || BATCH) ? 3 : 4;
 }
 
-template <typename R, bool ADVANCE, bool CONT, int L, bool ROLL>
+template <typename R, bool ADVANCE, bool CONT, int L, bool ROLL, int S>
 __global__ __launch_bounds__(kForceBlock, (force_waves<R, ROLL, false>())) void force_kick(Dev D, int p2, int p3, const int *src, int gmode) {
-  force_kick_body<R, ADVANCE, CONT, L, ROLL>(args_dev(), xcd_block(blockIdx.x, gridDim.x), p2, p3, src, gmode);
+  force_kick_body<R, ADVANCE, CONT, L, ROLL, S>(args_dev(), xcd_block(blockIdx.x, gridDim.x), p2, p3, src, gmode);
 }
 
 // ---------------------------------------------------------------------------
@@ -883,7 +915,7 @@ __global__ __launch_bounds__(kForceBlock, (force_waves<R, ROLL, true>())) void f
   const int b = (int)(m >> kBedShift), blk = (int)(m & kBlockMask);
   cDev &D = ((cDev *)tab)[b];
   const long long s = run[b].s + i;
-  force_kick_body<R, true, CONT, L, ROLL>(D, blk, (int)(s & 1), (int)(s % 3),
+  force_kick_body<R, true, CONT, L, ROLL, 1>(D, blk, (int)(s & 1), (int)(s % 3),
                                           i == 1 ? run[b].src : nullptr, grid_mode(i, n));
 }
 
@@ -997,48 +1029,68 @@ hipError_t launch_clear_grid(const Dev &D, long long s, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <typename R, bool ADVANCE, bool CONT, int L, bool ROLL>
+template <typename R, bool ADVANCE, bool CONT, int L, bool ROLL, int S>
 static void launch_fk(const Dev &D, int p2, int p3, const int *src, int gmode, hipStream_t st, hipEvent_t e0,
                       hipEvent_t e1) {
-  const int grid = (int)(((long long)D.n * L + kForceBlock - 1) / kForceBlock);
-  const size_t lds = force_lds_bytes(D.maxn, L);
+  const int grid = (int)(((long long)D.n * L * S + kForceBlock - 1) / kForceBlock);
+  const size_t lds = force_lds_bytes(D.maxn, L * S);
   if (e0)
-    hipExtLaunchKernelGGL(force_kick<R, ADVANCE, CONT, L, ROLL>, dim3(grid), dim3(kForceBlock), lds, st,
+    hipExtLaunchKernelGGL(force_kick<R, ADVANCE, CONT, L, ROLL, S>, dim3(grid), dim3(kForceBlock), lds, st,
                           e0, e1, 0, D, p2, p3, src, gmode);
   else
-    force_kick<R, ADVANCE, CONT, L, ROLL><<<grid, kForceBlock, lds, st>>>(D, p2, p3, src, gmode);
+    force_kick<R, ADVANCE, CONT, L, ROLL, S><<<grid, kForceBlock, lds, st>>>(D, p2, p3, src, gmode);
 }
 
-template <int L, bool ROLL>
+template <int L, bool ROLL, int S>
 static void launch_fk_lanes(const Dev &D, int p2, int p3, const int *src, int gmode, bool advance, bool cont,
                             bool fp32, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   if (!advance) {
     if (fp32)
-      launch_fk<float, false, false, L, ROLL>(D, p2, p3, src, gmode, st, e0, e1);
+      launch_fk<float, false, false, L, ROLL, S>(D, p2, p3, src, gmode, st, e0, e1);
     else
-      launch_fk<double, false, false, L, ROLL>(D, p2, p3, src, gmode, st, e0, e1);
+      launch_fk<double, false, false, L, ROLL, S>(D, p2, p3, src, gmode, st, e0, e1);
   } else if (fp32) {
     if (cont)
-      launch_fk<float, true, true, L, ROLL>(D, p2, p3, src, gmode, st, e0, e1);
+      launch_fk<float, true, true, L, ROLL, S>(D, p2, p3, src, gmode, st, e0, e1);
     else
-      launch_fk<float, true, false, L, ROLL>(D, p2, p3, src, gmode, st, e0, e1);
+      launch_fk<float, true, false, L, ROLL, S>(D, p2, p3, src, gmode, st, e0, e1);
   } else {
     if (cont)
-      launch_fk<double, true, true, L, ROLL>(D, p2, p3, src, gmode, st, e0, e1);
+      launch_fk<double, true, true, L, ROLL, S>(D, p2, p3, src, gmode, st, e0, e1);
     else
-      launch_fk<double, true, false, L, ROLL>(D, p2, p3, src, gmode, st, e0, e1);
+      launch_fk<double, true, false, L, ROLL, S>(D, p2, p3, src, gmode, st, e0, e1);
   }
+}
+
+// Lanes that share each of a particle's two parts of the list.  They find the
+// contacts of a part side by side and add them up in the list's order, so that
+// the result has the same bits for any number of them.  That shortens the
+// chain of a wavefront (one contact after the other, which is what a small bed
+// waits for) and takes as many more wavefronts: it pays until they fill the
+// SIMDs.  One, two and four lanes, us per step: 1,000 particles FP64 10.2, 8.7,
+// 8.0; 20k FP32 9.0, 8.6, 9.3; 37k FP64 with rolling friction 17.5, 16.2, 19.7;
+// 100k FP32 21.6, 23, 28.  Hence four while that is one wavefront per SIMD and
+// two up to two and a half.  A batch fills the chip with its beds and takes one.
+static int list_share(int n) {
+  constexpr long long kSimds = 1024;
+  const long long waves = (2ll * n + kForceBlock - 1) / kForceBlock;  // one lane for each part
+  return 4 * waves <= kSimds ? 4 : (4 * waves <= 5 * kSimds ? 2 : 1);
 }
 
 template <bool ROLL>
 static void launch_fk_roll(const Dev &D, int p2, int p3, const int *src, int gmode, bool advance, bool cont,
                            bool fp32, int lanes, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  const int share = lanes == 2 ? list_share(D.n) : 1;
   if (lanes == 1)
-    launch_fk_lanes<1, ROLL>(D, p2, p3, src, gmode, advance, cont, fp32, st, e0, e1);
+    launch_fk_lanes<1, ROLL, 1>(D, p2, p3, src, gmode, advance, cont, fp32, st, e0, e1);
   else if (lanes == 4)
-    launch_fk_lanes<4, ROLL>(D, p2, p3, src, gmode, advance, cont, fp32, st, e0, e1);
+    launch_fk_lanes<4, ROLL, 1>(D, p2, p3, src, gmode, advance, cont, fp32, st, e0, e1);
+  else if (share == 4)
+    launch_fk_lanes<2, ROLL, 4>(D, p2, p3, src, gmode, advance, cont, fp32, st, e0, e1);
+  else if (share == 2)
+    launch_fk_lanes<2, ROLL, 2>(D, p2, p3, src, gmode, advance, cont, fp32, st, e0, e1);
   else
-    launch_fk_lanes<2, ROLL>(D, p2, p3, src, gmode, advance, cont, fp32, st, e0, e1);
+    launch_fk_lanes<2, ROLL, 1>(D, p2, p3, src, gmode, advance, cont, fp32, st, e0, e1);
 }
 
 // e0/e1: when non-NULL, events recorded at the kernel's own start and end.

@@ -81,8 +81,8 @@ def main(argv=None):
     rows = _one(args.trace, "kernel_trace.csv")
     key = "Kernel_Name" if "Kernel_Name" in rows[0] else "Name"
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
-    prime_re = re.compile(rf"cfddem::force_kick<float, false, false, {lanes}, false>")
-    step_re = re.compile(rf"cfddem::force_kick<float, true, (true|false), {lanes}, false>")
+    prime_re = re.compile(rf"cfddem::force_kick<float, false, false, {lanes}, false, \d>")
+    step_re = re.compile(rf"cfddem::force_kick<float, true, (true|false), {lanes}, false, \d>")
     beds, cur = [], None
     for r in rows:
         if int(r.get("Grid_Size", r.get("Grid_Size_X", 0)) or 0) != grid:
@@ -128,8 +128,8 @@ def spouted(args, bench):
     key = "Kernel_Name" if "Kernel_Name" in rows[0] else "Name"
     gkey = "Grid_Size" if "Grid_Size" in rows[0] else "Grid_Size_X"
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
-    prime_re = re.compile(rf"cfddem::force_kick<float, false, false, {lanes}, false>")
-    step_re = re.compile(rf"cfddem::force_kick<float, true, (true|false), {lanes}, false>")
+    prime_re = re.compile(rf"cfddem::force_kick<float, false, false, {lanes}, false, \d>")
+    step_re = re.compile(rf"cfddem::force_kick<float, true, (true|false), {lanes}, false, \d>")
     starts = [i for i, r in enumerate(rows) if int(r[gkey] or 0) == grid and prime_re.search(r[key])]
     starts.append(len(rows))
     # the timed bed: the first bed at this grid that runs exactly warm-up +

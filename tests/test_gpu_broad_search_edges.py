@@ -1,12 +1,13 @@
 """Neighbour lists and carried histories where a broad search can go wrong:
 beds that rebuild their lists on almost every step, with list lengths that are
 no multiple of a lane's share, particles away from their home cell, unsorted
-beds, stencils cut off by every wall, and rolling friction."""
+beds, stencils cut off by every wall, and rolling friction; and the bed sizes at
+which more lanes share a list."""
 import numpy as np
 import pytest
 
-from paper_2211_01185_amd import synth
-from tests.parity_util import TOL, compare_contacts, compare_states, gpu_bed, gpu_state, oracle_bed
+from paper_2211_01185_amd import cfddem, synth
+from tests.parity_util import TOL, assert_close, compare_contacts, compare_states, gpu_bed, gpu_state, oracle_bed
 
 pytestmark = pytest.mark.gpu
 
@@ -55,3 +56,22 @@ def test_rebuilt_lists_have_the_same_bits_each_time(precision, lanes, mu_r):
         assert np.array_equal(a[k], b[k]), k
     for p, q in zip(ca, cb):
         assert np.array_equal(p, q)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n", [1, 8192, 8193, 40960, 40961])
+def test_sizes_where_more_lanes_share_a_list(n, precision):
+    """A single bed against a batch of one, which never shares a list's part."""
+    wl = _moving_lattice((32, 32, 41) if n > 8193 else (16, 16, 33), 0.1)
+    wl.x, wl.v, wl.w = wl.x[:, :n].copy(), wl.v[:, :n].copy(), wl.w[:, :n].copy()
+    wl.radius, wl.density = wl.radius[:n].copy(), wl.density[:n].copy()
+    single, other = gpu_bed(wl, precision, skin=1e-5), gpu_bed(wl, precision, skin=1e-5)
+    batch = cfddem.Batch([other])
+    single.step(3)
+    batch.step(3)
+    a, b = gpu_state(single), gpu_state(other)
+    for k in ("x", "v", "w", "Fc", "Tc"):
+        assert_close(k, a[k], b[k], 3 * TOL[precision])  # a single step's tolerance for each
+    for p, q in zip(single.read_contacts()[:2], other.read_contacts()[:2]):
+        assert np.array_equal(p, q)
+    assert single.poll()[0] == 0 and other.poll()[0] == 0
