@@ -413,14 +413,28 @@ __global__ void k_init(Dev D, const double *x, const double *v, const double *w,
   atomicMin(&rbits[1], bits);
 }
 
-__global__ void k_scatter_pos(int n, const int *oid, const dvec4 *src, double *dst) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+// The state read back in the order of the original IDs: block row 0 the
+// positions, 1 to 3 the velocities, spins and fluid forces (NULL: not wanted).
+// One launch for the four, which overlap (scattered 8-byte words: 27 us in four
+// launches and 21.6 in one for 150k particles, 23 and 14 for 100k).
+__global__ void k_scatter_state(int n, const int *oid, const dvec4 *pr, const double *v, const double *w,
+                                const double *ffp, double *x_out, double *v_out, double *w_out, double *ffp_out) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x, row = blockIdx.y;
   if (k >= n) return;
+  if (row == 0) {
+    if (!x_out) return;
+    const int o = oid[k];
+    const dvec4 p = pr[k];
+    x_out[o] = p.x;
+    x_out[n + o] = p.y;
+    x_out[2 * n + o] = p.z;
+    return;
+  }
+  const double *src = row == 1 ? v : (row == 2 ? w : ffp);
+  double *dst = row == 1 ? v_out : (row == 2 ? w_out : ffp_out);
+  if (!dst) return;
   const int o = oid[k];
-  const dvec4 p = src[k];
-  dst[o] = p.x;
-  dst[n + o] = p.y;
-  dst[2 * n + o] = p.z;
+  for (int c = 0; c < 3; ++c) dst[c * n + o] = src[c * n + k];
 }
 
 __global__ void k_scatter3(int n, const int *oid, const double *src, double *dst) {
@@ -1360,17 +1374,10 @@ dem_status dem_read_state(dem_ctx *ctx, double *x, double *v, double *omega, dou
   if (!ctx) return DEM_E_ARG;
   hipStream_t st = (hipStream_t)stream;
   const Dev &D = ctx->B.D;
-  if (x) {
-    k_scatter_pos<<<blocks(D.n, 256), 256, 0, st>>>(D.n, D.oid, D.pr[ctx->s & 1], x);
-    HIP_TRY(hipGetLastError());
-  }
-  const double *src[4] = {nullptr, D.v, D.w, D.ffp};
-  double *dst[4] = {nullptr, v, omega, f_fp};
-  for (int i = 1; i < 4; ++i) {
-    if (!dst[i]) continue;
-    k_scatter3<<<blocks(D.n, 256), 256, 0, st>>>(D.n, D.oid, src[i], dst[i]);
-    HIP_TRY(hipGetLastError());
-  }
+  if (!x && !v && !omega && !f_fp) return DEM_OK;
+  k_scatter_state<<<dim3(blocks(D.n, 256), 4), 256, 0, st>>>(D.n, D.oid, D.pr[ctx->s & 1], D.v, D.w, D.ffp, x, v,
+                                                             omega, f_fp);
+  HIP_TRY(hipGetLastError());
   return DEM_OK;
 }
 
