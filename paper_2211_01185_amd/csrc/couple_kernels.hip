@@ -910,7 +910,7 @@ int occ_grid(long long elems) {
 
 // Each group of NT threads takes one listed element at a time, up to
 // kMaxCoupleBlocks blocks (blocks past the list exit at once; dispatching one
-// block per mesh element would cost more than the work).  Longer lists are
+// block per element of a large mesh would cost more than the work).  Longer lists are
 // strided over the grid.
 template <typename R, int ORD, int MODE, int NT>
 __global__ __launch_bounds__(block_threads<NT>(), occ_waves<MODE>()) void couple_occupied(Dev D, Cpl C, int p2, int p3,
@@ -927,10 +927,13 @@ __global__ __launch_bounds__(block_threads<NT>(), occ_waves<MODE>()) void couple
   const int g = (int)threadIdx.x / NT;
   const int first = (int)blockIdx.x * kG + g;
   const int last = D.grid.n_elem - 1;
-  // the list entry is read in the same round trip as the list length (the
-  // list has n_elem entries)
-  const int nocc = min(D.err[kOccWord + parity], D.grid.n_elem);
-  const int e = D.occ[first < last ? first : last];
+  // parity < 0: every element, in order.  Otherwise the list entry is read in
+  // the same round trip as the list length (the list has n_elem entries)
+  int nocc = last + 1, e = first;
+  if (parity >= 0) {
+    nocc = min(D.err[kOccWord + parity], nocc);
+    e = D.occ[first < last ? first : last];
+  }
   __asm__ volatile("" ::: "memory");
   if ((int)blockIdx.x * kG >= nocc) return;  // whole block
   const int tid = threadIdx.x;
@@ -1099,14 +1102,27 @@ hipError_t launch_reset_count(int *cnt_words, hipStream_t st) {
 // Elements of one bed covered by one block of the classify pass.
 int couple_class_elems_per_block() { return kClassElems * (kClassBlock / kWave); }
 
+// A mesh of few elements is computed without the classification pass, a block
+// for each element: blocks of empty elements write their outputs and end while
+// the others wait for memory, and the pass is a launch of 4 us or more.  The
+// bound is the number of blocks the chip holds at once.  Pass and elements,
+// then elements alone: 4.3 + 10.7 and 11.7 us on 1,000 particles (Q1, FP64),
+// 5.7 + 10.4 and 10.0 on 2,000 (Q2, FP64), 5.5 + 9.4 and 8.9 on 20k (Q1, FP32).
+static bool couples_all(int ne, int nt) {
+  constexpr int kResident = 1024;
+  const int per = nt == 16 ? elems_per_block<16>() : (nt == 32 ? elems_per_block<32>() : 1);
+  return (ne + per - 1) / per <= kResident;
+}
+
 hipError_t launch_couple(const Dev &D, const Cpl &C, long long s, long long call, const double *U,
                          const double *P, double *eps_q, double *beta_q, double *fpf_q,
                          double *esums, bool fp32, hipStream_t st) {
-  const int p2 = (int)(s & 1), p3 = (int)(s % 3), parity = (int)(call & 1);
+  const int p2 = (int)(s & 1), p3 = (int)(s % 3);
   const int ne = D.grid.n_elem;
+  const int parity = couples_all(ne, C.elem_threads) ? -1 : (int)(call & 1);
   const int waves_c = (ne + kClassElems - 1) / kClassElems;
   const int grid_c = (waves_c + kClassBlock / kWave - 1) / (kClassBlock / kWave);
-  couple_classify<<<grid_c, kClassBlock, 0, st>>>(D, C, p3, parity, eps_q, beta_q, fpf_q, esums);
+  if (parity >= 0) couple_classify<<<grid_c, kClassBlock, 0, st>>>(D, C, p3, parity, eps_q, beta_q, fpf_q, esums);
   const int mode = cpl_mode_of(C.drag, C.shear || C.smooth);
   CFDDEM_DISPATCH((couple_occupied<RT_, O_, M_, NT_><<<occ_grid<NT_>(ne), block_threads<NT_>(), 0, st>>>(
                       D, C, p2, p3, parity, U, P, eps_q, beta_q, fpf_q, esums)),

@@ -1,0 +1,38 @@
+"""Coupling steps at the mesh sizes where the classification pass comes in
+(1,024 blocks of elements) and mostly empty meshes, against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2211_01185_amd import synth
+from tests.parity_util import TOL, assert_close, gpu_bed, gpu_state, oracle_bed
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,elem_threads,n_el", [
+    (1, 128, [1, 1, 1]), (300, 128, [16, 8, 8]), (300, 128, [5, 5, 41]), (300, 64, [16, 8, 8]), (300, 64, [5, 5, 41]),
+    (300, 32, [16, 16, 8]), (300, 32, [5, 10, 41]), (300, 16, [16, 16, 16]), (300, 16, [10, 10, 41])])
+def test_meshes_with_and_without_classification(n, elem_threads, n_el, precision):
+    wl = synth.plain(n=n)
+    lo, hi = wl.dem["box_lo"], wl.dem["box_hi"]
+    wl.fluid["n_el"] = n_el
+    nodes = synth.node_grid(lo, hi, n_el, 2)
+    wl.U = np.stack([0.1 * nodes[1], 0.0 * nodes[0], 0.5 + nodes[2]])
+    wl.P = 100.0 * (1.0 - synth.node_grid(lo, hi, n_el, 1)[2] / hi[2])
+    gb = gpu_bed(wl, precision, elem_threads=elem_threads)
+    ob, fl = oracle_bed(wl)
+    U, P = (torch.as_tensor(f, dtype=torch.float64, device="cuda").contiguous() for f in (wl.U, wl.P))
+    tol = TOL[precision]
+    for step in range(3):  # a single step's tolerance for each
+        out, ref = gb.couple(U, P, elem_sums=True), ob.couple(fl, wl.U, wl.P)
+        assert np.array_equal(out["elem_sums"][0].cpu().numpy(), ref["elem_sums"][0])
+        assert_close("eps_q", out["eps_q"].cpu().numpy(), ref["eps_q"], 1e-12 * (1 + step))
+        for k in ("beta_q", "fpf_q"):
+            assert_close(k, out[k].cpu().numpy(), ref[k], tol * (1 + step))
+        assert_close("f_fp", gpu_state(gb)["ffp"], ob.state()["ffp"], tol * (1 + step))
+        gb.step(1)
+        ob.step(1)
+    assert gb.poll()[0] == 0
