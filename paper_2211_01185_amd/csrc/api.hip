@@ -813,6 +813,8 @@ __global__ void k_restore_words(int *err, int lb_word, int cur, int bits) {
   for (int i = 0; i < 3; ++i) err[kFlagWord + i] = 0;
   err[kOccWord] = 0;
   err[kOccWord + 1] = 0;
+  err[kOccWord + 2] = 0;
+  err[kOccWord + 3] = 0;
   err[kLbufWord + lb_word] = cur;
   err[0] = bits;
 }

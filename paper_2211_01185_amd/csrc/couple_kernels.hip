@@ -802,6 +802,25 @@ __device__ __forceinline__ void couple_element(const Dev &D, const Cpl &C, int e
   cpl_sync<NT>();  // the LDS is reused for the next element
 }
 
+// Elements of at most kFew particles are computed by groups of kFew threads,
+// several in a wavefront, also where more threads per element were asked for:
+// the others would have nothing to do, and the sums, whose butterfly skips the
+// levels without particles, are the same.
+// Q1 only: of the 109 outputs of a Q2 element each thread of so small a group
+// stores seven, which takes longer than the particles (the fluidized Q2 bed
+// with some such elements at its surface would go from 14.7 to 17.5 us).  And
+// only where there are enough of them, for a group's chain is the longer one.
+// A suspension of 150k particles, 9 in each element (Q1, FP64): 81.3 -> 35.1 us.
+constexpr int kFew = 16;
+constexpr int kFewMin = 2048;
+static bool splits_few(int order, int nt) { return order == 1 && nt != 16 && nt != 32; }
+// tot with min(m, kFew + 1) more in the half at `shift` (at most 64 lanes are
+// added up later), which stays at most kFew + 1.
+__device__ inline unsigned min_few(unsigned tot, int m, int shift) {
+  const unsigned v = min((tot >> shift & 0xffffu) + (unsigned)min(m, kFew + 1), kFew + 1u);
+  return (tot & ~(0xffffu << shift)) | v << shift;
+}
+
 // Classification of kClassElems consecutive elements starting at e0 by one
 // wavefront: empty ones get their outputs, occupied ones are appended to
 // list (cap entries; entries tag | element) through the counter at cnt_word,
@@ -810,9 +829,11 @@ __device__ __forceinline__ void couple_element(const Dev &D, const Cpl &C, int e
 // counter takes one atomic per block (a device-wide counter is a single
 // address that every XCD contends for: one atomic per wavefront serializes a
 // large mesh).
-// Called by every thread of the block; s_cnt is LDS of kClassBlock / kWave + 1
-// ints.  The order of the list does not matter: each listed element is
+// Called by every thread of the block; s_cnt is LDS of kClassBlock / kWave + 2
+// ints.  SPLIT: elements of more than kFew particles are listed from the end of
+// the list, through the counter two words further on.  The order of the list does not matter: each listed element is
 // computed on its own.
+template <bool SPLIT>
 __device__ __forceinline__ void couple_classify_body(const Dev &D, const Cpl &C, int e0, int p3,
                                                      int *cnt_word, unsigned *list, long long cap,
                                                      unsigned tag,
@@ -825,7 +846,8 @@ __device__ __forceinline__ void couple_classify_body(const Dev &D, const Cpl &C,
   const int wave = threadIdx.x / kWave;
   const Grid &G = D.grid;
   const int ne = e0 >= G.n_elem ? 0 : (G.n_elem - e0 < kClassElems ? G.n_elem - e0 : kClassElems);
-  unsigned occupied = 0;
+  unsigned occupied = 0, crowded = 0;
+  unsigned tot2[kClassElems / 2] = {};  // particles of two elements each, the cells' counts cut off past kFew
   if (ne > 0) {  // whole wavefront
     const gptr<const int> cnt = gsel(D.cnt, p3);
     for (int c = lane; c - lane < G.kk; c += kWave) {
@@ -836,6 +858,17 @@ __device__ __forceinline__ void couple_classify_body(const Dev &D, const Cpl &C,
 #pragma unroll
       for (int j = 0; j < kClassElems; ++j)
         if (__ballot(m[j] != 0)) occupied |= 1u << j;
+      if constexpr (SPLIT)
+#pragma unroll
+        for (int j = 0; j < kClassElems; ++j) tot2[j / 2] = min_few(tot2[j / 2], m[j], 16 * (j & 1));
+    }
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int j = 0; j < kClassElems / 2; ++j) {
+        for (int off = 1; off < kWave; off <<= 1) tot2[j] += __shfl_xor(tot2[j], off, kWave);
+        crowded |= (tot2[j] & 0xffffu) > kFew ? 1u << (2 * j) : 0u;
+        crowded |= (tot2[j] >> 16) > kFew ? 2u << (2 * j) : 0u;
+      }
     }
     // empty elements: eps = 1, no drag, nothing handed to the fluid; their
     // quadrature points form contiguous runs
@@ -854,34 +887,48 @@ __device__ __forceinline__ void couple_classify_body(const Dev &D, const Cpl &C,
     if (esums && lane < ne && !((occupied >> lane) & 1u))
       for (int k = 0; k < 12; ++k) glb(esums)[(long)k * G.n_elem + e0 + lane] = 0.0;
   }
-  if (lane == 0) s_cnt[wave] = __popc(occupied);
+  const unsigned few = occupied & ~crowded;
+  // counts of the wavefronts, then the block's places: elements of few
+  // particles (all, without SPLIT) in the low half, crowded ones in the high
+  if (lane == 0) s_cnt[wave] = __popc(few) | __popc(crowded) << 16;
   __syncthreads();
   if (threadIdx.x == 0) {
     int tot = 0;
     for (int w = 0; w < kWaves; ++w) tot += s_cnt[w];
-    s_cnt[kWaves] = tot > 0 ? __hip_atomic_fetch_add(glb(cnt_word), tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    const int nf = tot & 0xffff, nc = tot >> 16;
+    s_cnt[kWaves] = nf > 0 ? __hip_atomic_fetch_add(glb(cnt_word), nf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    if (SPLIT)
+      s_cnt[kWaves + 1] =
+          nc > 0 ? __hip_atomic_fetch_add(glb(cnt_word + 2), nc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
   }
   __syncthreads();
   if (occupied) {
-    int base = s_cnt[kWaves];
-    for (int w = 0; w < wave; ++w) base += s_cnt[w];
-    const int at = base + __popc(occupied & ((1u << lane) - 1u));
-    if (lane < ne && ((occupied >> lane) & 1u) && at < cap) glb(list)[at] = tag | (unsigned)(e0 + lane);
+    int before = 0;
+    for (int w = 0; w < wave; ++w) before += s_cnt[w];
+    const unsigned below = (1u << lane) - 1u;
+    const int at = s_cnt[kWaves] + (before & 0xffff) + __popc(few & below);
+    if (lane < ne && ((few >> lane) & 1u) && at < cap) glb(list)[at] = tag | (unsigned)(e0 + lane);
+    if (SPLIT) {
+      const int back = s_cnt[kWaves + 1] + (before >> 16) + __popc(crowded & below);
+      if (lane < ne && ((crowded >> lane) & 1u) && back < cap) glb(list)[cap - 1 - back] = tag | (unsigned)(e0 + lane);
+    }
   }
 }
 
-// Single bed.  Occupied-element counts live in two words selected by the
+// Single bed.  Elements of few particles are listed from the front, crowded
+// ones (two words further on) from the back.  Occupied-element counts live in two words selected by the
 // parity of the coupling call: call k appends to word k&1 and clears word
 // (k+1)&1 for the next call, which nothing reads during call k.
+template <bool SPLIT>
 __global__ __launch_bounds__(kClassBlock) void couple_classify(Dev D, Cpl C, int p3, int parity,
                                                                double *__restrict__ eps_q,
                                                                double *__restrict__ beta_q,
                                                                double *__restrict__ fpf_q,
                                                                double *__restrict__ esums) {
-  __shared__ int s_cnt[kClassBlock / kWave + 1];
+  __shared__ int s_cnt[kClassBlock / kWave + 2];
   const int gw = (blockIdx.x * kClassBlock + threadIdx.x) / kWave;
-  if (gw == 0 && threadIdx.x == 0) D.err[kOccWord + (parity ^ 1)] = 0;
-  couple_classify_body(D, C, gw * kClassElems, p3, D.err + kOccWord + parity, (unsigned *)D.occ,
+  if (gw == 0 && threadIdx.x == 0) D.err[kOccWord + (parity ^ 1)] = D.err[kOccWord + 2 + (parity ^ 1)] = 0;
+  couple_classify_body<SPLIT>(D, C, gw * kClassElems, p3, D.err + kOccWord + parity, (unsigned *)D.occ,
                        D.grid.n_elem, 0u, eps_q, beta_q, fpf_q, esums, s_cnt);
 }
 
@@ -945,6 +992,42 @@ __global__ __launch_bounds__(block_threads<NT>(), occ_waves<MODE>()) void couple
     couple_element<R, ORD, MODE, NT>(D, C, D.occ[i], U, P, eps_q, beta_q, fpf_q, esums, p2, p3, sh[g], sLq);
 }
 
+// The same with the elements of few particles apart: crowded ones, from the
+// end of the list, by the whole block, then the others (in groups, when there
+// are kFewMin of them).
+template <typename R, int ORD, int MODE, int NT>
+__global__ __launch_bounds__(block_threads<NT>(), occ_waves<MODE>()) void couple_occupied_few(
+    Dev D, Cpl C, int p2, int p3, int parity, const double *__restrict__ U, const double *__restrict__ P,
+    double *__restrict__ eps_q, double *__restrict__ beta_q, double *__restrict__ fpf_q,
+    double *__restrict__ esums) {
+  constexpr int kGroups = NT / kFew;  // elements of few particles a block takes at once
+  __shared__ union {
+    CplShared<NT> sh;
+    CplShared<kFew> few[kGroups];
+  } u;
+  __shared__ double sLq[NT / kWave][3][3];  // 1D velocity basis at the Gauss points, for each wavefront
+  const int first = (int)blockIdx.x;
+  const int last = D.grid.n_elem - 1;
+  const int nfew = min(D.err[kOccWord + parity], last + 1);
+  const int ncrowd = min(D.err[kOccWord + 2 + parity], last + 1 - nfew);
+  const int e0 = D.occ[last - min(first, last)];
+  __asm__ volatile("" ::: "memory");
+  if (first >= ncrowd + nfew) return;  // whole block
+  const int tid = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  if (tid < 9) sLq[wave][tid / 3][tid % 3] = C.Lq[tid / 3][tid % 3];  // read after the element's first barrier
+  const int whole = ncrowd + (nfew < kFewMin ? nfew : 0);
+  int i = first;
+  for (; i < whole; i += (int)gridDim.x) {
+    const int e = i == first && i < ncrowd ? e0 : D.occ[i < ncrowd ? last - i : i - ncrowd];
+    couple_element<R, ORD, MODE, NT>(D, C, e, U, P, eps_q, beta_q, fpf_q, esums, p2, p3, u.sh, sLq[wave]);
+  }
+  if (nfew < kFewMin) return;
+  // no block barrier from here on
+  const int g = (int)threadIdx.x / kFew;
+  for (int k = (i - whole) * kGroups + g; k < nfew; k += (int)gridDim.x * kGroups)
+    couple_element<R, ORD, MODE, kFew>(D, C, D.occ[k], U, P, eps_q, beta_q, fpf_q, esums, p2, p3, u.few[g], sLq[wave]);
+}
+
 // ---------------------------------------------------------------------------
 // batched coupling: every bed of a batch, one occupied-element list
 // ---------------------------------------------------------------------------
@@ -952,7 +1035,7 @@ __global__ __launch_bounds__(kClassBlock) void couple_classify_batch(
     const Dev *__restrict__ tab, const Cpl *__restrict__ ctab, const CplIO *__restrict__ iot,
     const BedRun *__restrict__ run, const unsigned *__restrict__ map, int *cnt_words, unsigned *list,
     ModeLists ml, long long list_len) {
-  __shared__ int s_cnt[kClassBlock / kWave + 1];
+  __shared__ int s_cnt[kClassBlock / kWave + 2];
   const unsigned mb = map[blockIdx.x];
   const int b = (int)(mb >> kBedShift), blk = (int)(mb & kBlockMask);
   const Dev &D = tab[b];
@@ -963,7 +1046,7 @@ __global__ __launch_bounds__(kClassBlock) void couple_classify_batch(
   // occupied elements go to the list of the bed's element-kernel variant
   const int m = cpl_mode_of(C.drag, C.shear || C.smooth);
   const long long cap = (m < 2 ? ml.off[m + 1] : list_len) - ml.off[m];
-  couple_classify_body(D, C, gw * kClassElems, p3, cnt_words + m, list + ml.off[m], cap,
+  couple_classify_body<false>(D, C, gw * kClassElems, p3, cnt_words + m, list + ml.off[m], cap,
                        (unsigned)b << kBedShift, io.eps_q, io.beta_q, io.fpf_q, io.esums, s_cnt);
 }
 
@@ -1122,8 +1205,31 @@ hipError_t launch_couple(const Dev &D, const Cpl &C, long long s, long long call
   const int parity = couples_all(ne, C.elem_threads) ? -1 : (int)(call & 1);
   const int waves_c = (ne + kClassElems - 1) / kClassElems;
   const int grid_c = (waves_c + kClassBlock / kWave - 1) / (kClassBlock / kWave);
-  if (parity >= 0) couple_classify<<<grid_c, kClassBlock, 0, st>>>(D, C, p3, parity, eps_q, beta_q, fpf_q, esums);
   const int mode = cpl_mode_of(C.drag, C.shear || C.smooth);
+  if (parity >= 0 && splits_few(C.order, C.elem_threads)) {
+    couple_classify<true><<<grid_c, kClassBlock, 0, st>>>(D, C, p3, parity, eps_q, beta_q, fpf_q, esums);
+#define CFDDEM_FEW(R, M)                                                                                        \
+  do {                                                                                                          \
+    if (C.elem_threads == 64)                                                                                   \
+      couple_occupied_few<R, 1, M, 64><<<occ_grid<64>(ne), 64, 0, st>>>(D, C, p2, p3, parity, U, P, eps_q,      \
+                                                                        beta_q, fpf_q, esums);                  \
+    else                                                                                                        \
+      couple_occupied_few<R, 1, M, 128><<<occ_grid<128>(ne), 128, 0, st>>>(D, C, p2, p3, parity, U, P, eps_q,   \
+                                                                           beta_q, fpf_q, esums);               \
+  } while (0)
+    if (fp32) {
+      if (mode == 2) CFDDEM_FEW(float, 2);
+      else if (mode == 1) CFDDEM_FEW(float, 1);
+      else CFDDEM_FEW(float, 0);
+    } else {
+      if (mode == 2) CFDDEM_FEW(double, 2);
+      else if (mode == 1) CFDDEM_FEW(double, 1);
+      else CFDDEM_FEW(double, 0);
+    }
+#undef CFDDEM_FEW
+    return hipGetLastError();
+  }
+  if (parity >= 0) couple_classify<false><<<grid_c, kClassBlock, 0, st>>>(D, C, p3, parity, eps_q, beta_q, fpf_q, esums);
   CFDDEM_DISPATCH((couple_occupied<RT_, O_, M_, NT_><<<occ_grid<NT_>(ne), block_threads<NT_>(), 0, st>>>(
                       D, C, p2, p3, parity, U, P, eps_q, beta_q, fpf_q, esums)),
                   fp32, C.order, mode, C.elem_threads);

@@ -36,3 +36,44 @@ def test_meshes_with_and_without_classification(n, elem_threads, n_el, precision
         gb.step(1)
         ob.step(1)
     assert gb.poll()[0] == 0
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("elem_threads", [32, 64, 128])
+@pytest.mark.parametrize("nz", [30, 34])
+def test_elements_of_few_particles_beside_crowded_ones(nz, elem_threads, precision):
+    """Q1 meshes of 1,920 and 2,176 elements with one particle each, some with
+    none, 15, 16, 17, 18 and 100: the few-particle groups' bounds."""
+    wl = synth.plain(n=2)
+    n_el, hi = [8, 8, nz], np.array(wl.dem["box_hi"])
+    h = hi / n_el
+    e = np.arange(64 * nz)
+    count = np.ones(e.size, dtype=int)
+    count[[0, 7, 70, 500, 501, 900, 1300, 64 * nz - 1]] = [17, 16, 18, 0, 100, 15, 17, 16]
+    rng = np.random.default_rng(5)
+    x = []
+    for i in e:
+        base = np.array([i % 8, (i // 8) % 8, i // 64])
+        k = rng.permutation(125)[:count[i]]
+        cell = (np.stack([k % 5, (k // 5) % 5, k // 25], 1) + rng.uniform(0.4, 0.6, (k.size, 3))) / 5
+        x.append((base + cell) * h)
+    x = np.concatenate(x)[rng.permutation(count.sum())]
+    wl.x = np.ascontiguousarray(x.T)
+    n = wl.x.shape[1]
+    wl.v, wl.w = rng.normal(0.0, 0.1, (3, n)), np.zeros((3, n))
+    wl.radius, wl.density = np.full(n, 0.4e-3), np.full(n, 2500.0)
+    wl.fluid.update(order=1, n_el=n_el)
+    nodes = synth.node_grid(wl.dem["box_lo"], hi, n_el, 1)
+    wl.U = np.stack([0.1 * nodes[1], 0.0 * nodes[0], 0.5 + nodes[2]])
+    wl.P = 100.0 * (1.0 - nodes[2] / hi[2])
+    gb = gpu_bed(wl, precision, elem_threads=elem_threads)
+    ob, fl = oracle_bed(wl)
+    U, P = (torch.as_tensor(f, dtype=torch.float64, device="cuda").contiguous() for f in (wl.U, wl.P))
+    for _ in range(2):
+        out, ref = gb.couple(U, P, elem_sums=True), ob.couple(fl, wl.U, wl.P)
+        assert np.array_equal(out["elem_sums"][0].cpu().numpy(), ref["elem_sums"][0])
+        assert_close("eps_q", out["eps_q"].cpu().numpy(), ref["eps_q"], 1e-12)
+        for k in ("beta_q", "fpf_q"):
+            assert_close(k, out[k].cpu().numpy(), ref[k], TOL[precision])
+        assert_close("f_fp", gpu_state(gb)["ffp"], ob.state()["ffp"], TOL[precision])
+    assert gb.poll()[0] == 0
