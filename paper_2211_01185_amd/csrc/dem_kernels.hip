@@ -502,7 +502,8 @@ struct Entry {
   double h[3];
 };
 // b comes from a list entry; an index outside [0, n) (only a slot past the
-// list's length can hold one) reads the particle itself.
+// list's length can hold one) reads the particle itself.  t is a slot of the
+// list's capacity.
 __device__ __forceinline__ Entry load_entry(gptr<const dvec4> P, gptr<const dvec4> VM, gptr<const dvec4> WS,
                                             gptr<const double> hdt, int n, int a, int b, int t) {
   b = (unsigned)b < (unsigned)n ? b : a;
@@ -687,9 +688,12 @@ __device__ __forceinline__ void force_kick_body(cDev &D, int blk, int p2, int p3
   const int last = D.maxn - 1;
   for (int t = first; t - V * sub < m; t += L) {
     // one round trip per entry: the partner's records, this entry's stored
-    // tangential overlap and the next entry's key (its slot clamped to the
-    // list capacity; past the list's length its value is not used)
-    const Entry cur_e = load_entry(P, VM, WS, hdt, n, a, (int)(unsigned)(key & 0xffffffffu), t);
+    // tangential overlap and the next entry's key.  Of the lanes sharing a part
+    // (S > 1) some stand past the list's end in its last round, by up to
+    // V (S - 1) entries, so both slots are clamped to the list capacity (past
+    // the list's length their values are not used)
+    const Entry cur_e =
+        load_entry(P, VM, WS, hdt, n, a, (int)(unsigned)(key & 0xffffffffu), S == 1 ? t : min(t, last));
     key = lst[(size_t)min(t + L, last) * n + a];
     const dvec4 pb = cur_e.p, vb = cur_e.v, wb = cur_e.w;
     const double rb = pb.w;

@@ -75,3 +75,24 @@ def test_sizes_where_more_lanes_share_a_list(n, precision):
     for p, q in zip(single.read_contacts()[:2], other.read_contacts()[:2]):
         assert np.array_equal(p, q)
     assert single.poll()[0] == 0 and other.poll()[0] == 0
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n_side", [(6, 6, 6), (21, 21, 20)])  # four and two lanes share a list's part
+def test_full_lists_shared_by_more_lanes(n_side, precision):
+    """Lists of the capacity's length, the last round of which leaves some of
+    the sharing lanes past the list's end, from a capacity of one entry on."""
+    wl = synth.lattice(n_side=n_side)
+    for keep, longest in ((None, 6), (2, 1)):  # the whole lattice; two neighbours of it
+        if keep:
+            wl.x, wl.v, wl.w = wl.x[:, :keep].copy(), wl.v[:, :keep].copy(), wl.w[:, :keep].copy()
+            wl.radius, wl.density = wl.radius[:keep].copy(), wl.density[:keep].copy()
+        gb = gpu_bed(wl, precision, max_neighbors=longest)
+        ob, _ = oracle_bed(wl)
+        for steps in (0, 1, 2):
+            gb.step(steps)
+            ob.step(steps)
+            tol = (1 + steps) * TOL[precision]  # a single step's tolerance for each
+            compare_contacts(gb, ob, tol)
+            compare_states(gb, ob, tol, keys=("x", "v", "w", "Fc", "Tc"))
+        assert gb.poll()[0] == 0
