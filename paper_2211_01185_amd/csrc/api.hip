@@ -263,6 +263,14 @@ dem_status derive(const dem_params *dp, const cfd_params *cp, Sizes &S) {
   return DEM_OK;
 }
 
+// Dev::reach of a bed whose largest radius is r_max.  The margin covers the
+// rounding of cell faces and of the binning.
+double search_reach(const Sizes &S, double r_max) {
+  double reach = r_max + S.skin;
+  for (int a = 0; a < 3; ++a) reach += 1e-6 * S.grid.hc[a] + 1e-14 * (fabs(S.grid.lo[a]) + fabs(S.grid.hi[a]));
+  return reach;
+}
+
 // Workspace carving: every array 256-byte aligned.
 struct Carver {
   char *base;
@@ -287,7 +295,7 @@ struct Buffers {
   int *start;                   // first sorted index of each cell (re-sort)
   long long *cnt64, *off64;     // per-particle contact counts / offsets
   long long *bsum;              // per-block partial sums of the device scan
-  unsigned long long *scalars;  // [0] contact count, [1] radius max bits, [2] radius min bits
+  unsigned long long *scalars;  // [0] contact count or radius max bits, [1] radius min bits
   double *energy;               // per-block kinetic energies, then the two totals
   double *metrics;              // per-block metric partials, then the seven results
   // smoothed void fraction (only when enabled): fixed-point element volume
@@ -411,6 +419,13 @@ __global__ void k_init(Dev D, const double *x, const double *v, const double *w,
                                 : 0x7ff8000000000000ULL;
   atomicMax(&rbits[0], bits);
   atomicMin(&rbits[1], bits);
+}
+
+// Largest radius (bits of a non-negative double; anything else as a NaN).
+__global__ void k_radius_max(int n, const double *r, unsigned long long *rbits) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= n) return;
+  atomicMax(rbits, r[k] >= 0.0 ? (unsigned long long)__double_as_longlong(r[k]) : 0x7ff8000000000000ULL);
 }
 
 // The state read back in the order of the original IDs: block row 0 the
@@ -1114,6 +1129,13 @@ dem_status dem_write_state(dem_ctx *ctx, const void *src, size_t bytes, void *st
   }
   k_restore_words<<<1, 64, 0, st>>>(D.err, (int)((h.s + 1) % 3), h.lbuf, h.err);
   HIP_TRY(hipGetLastError());
+  // the radii are the checkpoint's, also where the context was created with a
+  // smaller d_max (whose cells were as wide): the searches reach for them
+  k_fill_u64<<<1, 64, 0, st>>>(ctx->B.scalars, 0ULL, 0ULL);
+  k_radius_max<<<blocks(D.n, 256), 256, 0, st>>>(D.n, D.rad, ctx->B.scalars);
+  HIP_TRY(hipGetLastError());
+  unsigned long long rbits = 0;
+  HIP_TRY(hipMemcpyAsync(&rbits, ctx->B.scalars, sizeof rbits, hipMemcpyDeviceToHost, st));
   // the checkpoint's particle order is not a re-sort's: no home cells
   HIP_TRY(clear_epoch(D, st));
   HIP_TRY(launch_drift_bin(D, h.s, false, false, true, st));
@@ -1122,6 +1144,9 @@ dem_status dem_write_state(dem_ctx *ctx, const void *src, size_t bytes, void *st
   ctx->pending_src = nullptr;
   ctx->poisoned = err_to_status(h.err);
   HIP_TRY(hipStreamSynchronize(st));
+  double r_max;
+  memcpy(&r_max, &rbits, sizeof r_max);
+  D.reach = search_reach(ctx->S, r_max);
   return DEM_OK;
 }
 
@@ -1158,10 +1183,7 @@ dem_status dem_create(const dem_params *dp, const cfd_params *cp, const double *
   D.maxn = S.maxn;
   D.skin = S.skin;
   D.trig2 = (0.499 * S.skin) * (0.499 * S.skin);
-  // the margin covers the rounding of cell faces and of the binning
-  D.reach = 0.5 * dp->d_max + S.skin;
-  for (int a = 0; a < 3; ++a)
-    D.reach += 1e-6 * S.grid.hc[a] + 1e-14 * (fabs(S.grid.lo[a]) + fabs(S.grid.hi[a]));
+  D.reach = search_reach(S, 0.5 * dp->d_max);
   D.dt = dp->dt;
   for (int a = 0; a < 3; ++a) D.g[a] = dp->gravity[a];
   D.grid = S.grid;

@@ -98,3 +98,31 @@ def test_restore_refuses_another_shape():
     with pytest.raises(cfddem.CfddemError) as ei:
         a.restore(bad)
     assert ei.value.status == cfddem.DEM_E_ABI
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_restore_into_a_bed_created_with_smaller_spheres(precision):
+    """Cells of 3.17 mm in both (element 9.5 mm, spheres of 3 and 2.5 mm): the
+    restored spheres find every partner that the writer's do."""
+    wl = synth.lattice(n_side=(9, 8, 10))
+    wl.v[:] = np.random.default_rng(7).normal(0.0, 0.3, wl.v.shape)
+    wl.dem["box_hi"], wl.fluid["n_el"] = [0.038, 0.038, 0.038], [4, 4, 4]
+    kw = dict(skin=1e-5, cell_capacity=32, resort_every=5)
+    a = cfddem.bed_from_workload(wl, precision=precision, **kw)
+    a.step(7)
+    blob = a.checkpoint()
+    a.step(20)
+    wl.radius[:] *= 2.5 / 3.0
+    b = cfddem.bed_from_workload(wl, precision=precision, **kw)
+    b.restore(blob)
+    b.step(20)
+    _same(_snapshot(a), _snapshot(b))
+    assert len(_snapshot(a)["pairs_i"]) > 1000
+    assert a.poll()[0] == 0 and b.poll()[0] == 0
+    # and back: the smaller spheres' own checkpoint into the larger ones' bed
+    c = cfddem.bed_from_workload(wl, precision=precision, **kw)
+    blob = c.checkpoint()
+    a.restore(blob)
+    a.step(20)
+    c.step(20)
+    _same(_snapshot(a), _snapshot(c))
