@@ -82,7 +82,13 @@ __device__ __forceinline__ double recip(double x) {  // 1 / x, x > 0 and normal
 }
 __device__ __forceinline__ double quot(double a, double x, double inv) {  // a / x, inv: 1 / x within a few ulp
   const double q = a * inv;
-  return fma(fma(-q, x, a), inv, q);
+  return fma(-fma(q, x, -a), inv, q);  // this sign of the residual keeps a zero's
+}
+// The same for any a: a quotient that is not finite, whose residual would be a
+// NaN, is left as it is.
+__device__ __forceinline__ double quot_any(double a, double x, double inv) {
+  const double q = a * inv, r = fma(-fma(q, x, -a), inv, q);
+  return fabs(q) < __builtin_inf() ? r : q;
 }
 __device__ __forceinline__ double root(double x, double &inv) {  // sqrt(x), inv: its reciprocal within 2 ulp
   const double y = __builtin_amdgcn_rsq(x);
@@ -134,8 +140,8 @@ __device__ __forceinline__ void drift_bin_body(cDev &D, int k, int p2, int p3, i
     double vhc[3], whc[3];
     for (int c = 0; c < 3; ++c) {
       const int i = c * n + k;
-      const double acc = quot(glb(D.Fc)[i] + glb(D.ffp)[i], m, im) + D.g[c];
-      const double alpha = quot(glb(D.Tc)[i], inertia, ii);
+      const double acc = quot_any(glb(D.Fc)[i] + glb(D.ffp)[i], m, im) + D.g[c];
+      const double alpha = quot_any(glb(D.Tc)[i], inertia, ii);
       vhc[c] = glb(D.v)[i] + 0.5 * D.dt * acc;
       whc[c] = glb(D.w)[i] + 0.5 * D.dt * alpha;
       xp[c] = x0[c] + D.dt * vhc[c];
@@ -805,8 +811,8 @@ __device__ __forceinline__ void force_kick_body(cDev &D, int blk, int p2, int p3
     double vb[3], wb[3], acc[3], alpha[3];
     for (int c = 0; c < 3; ++c) {
       const int i = c * n + a;
-      acc[c] = quot(F[c] + fa[c], ma, im) + D.g[c];
-      alpha[c] = quot(T[c], inertia, ii);
+      acc[c] = quot_any(F[c] + fa[c], ma, im) + D.g[c];
+      alpha[c] = quot_any(T[c], inertia, ii);
       vb[c] = (c == 0 ? va0 : (c == 1 ? va1 : va2)) + 0.5 * D.dt * acc[c];
       wb[c] = (c == 0 ? wa0 : (c == 1 ? wa1 : wa2)) + 0.5 * D.dt * alpha[c];
       if (!CONT) {

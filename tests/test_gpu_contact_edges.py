@@ -68,3 +68,45 @@ def test_coincident_centres_are_an_error(precision):
     gb.step(1)
     err, _ = gb.poll()
     assert err == cfddem.DEM_E_NAN
+
+
+def _kicked(precision, force, torque, mass):
+    """Quotients force / mass and torque / (0.4 mass r r) as a DEM step takes
+    them: 1,000 spheres at rest out of each other's reach, without gravity, the
+    held fluid force, the stored torque and the mass put into a checkpoint.
+    With a time step that is a power of two the step's two half kicks of equal
+    size (one for the torque, whose new value is zero) scale them exactly."""
+    torch = pytest.importorskip("torch")
+    wl = synth.lattice(n_side=(10, 10, 10), spacing_factor=1.5)
+    dt = 2.0 ** -17
+    wl.dem.update(dt=dt, gravity=[0.0, 0.0, 0.0])
+    wl.x[2] += 1e-3  # off the floor
+    wl.v[:] = 0.0
+    wl.w[:] = 0.0
+    gb = gpu_bed(wl, precision)
+    blob = gb.checkpoint().cpu()
+    at, n = 256, wl.n
+    for name, size in [("pr", 32), ("v", 24), ("w", 24), ("Fc", 24), ("Tc", 24), ("ffp", 24), ("rad", 8), ("mass", 8)]:
+        new = {"Tc": torque, "ffp": force, "mass": mass}.get(name)
+        if new is not None:
+            blob[at:at + size * n] = torch.from_numpy(np.ascontiguousarray(new).view(np.uint8).reshape(-1))
+        at = (at + size * n + 255) // 256 * 256
+    gb.restore(blob)
+    gb.step(1)
+    st = gpu_state(gb)
+    return st["v"] / dt, st["w"] / (0.5 * dt), 0.4 * mass * wl.radius * wl.radius, gb
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_infinite_and_overflowing_quotients(precision):
+    """An infinite torque, or one whose quotient overflows, gives an infinite
+    spin, not a NaN (an infinite force puts its sphere at an infinite overlap
+    with a wall within the step, which is a NaN by itself)."""
+    for big in (np.inf, -np.inf, 1e308, -1e308):
+        torque, mass = np.zeros((3, 1000)), np.full(1000, 3e-5)
+        torque[2, 499] = big
+        v, w, inertia, gb = _kicked(precision, np.zeros((3, 1000)), torque, mass)
+        with np.errstate(over="ignore"):
+            assert np.array_equal(w, torque / inertia)
+        assert np.max(np.abs(v)) == 0.0
+        assert gb.poll()[0] == 0
