@@ -805,15 +805,30 @@ __device__ __forceinline__ void couple_element(const Dev &D, const Cpl &C, int e
 // Elements of at most kFew particles are computed by groups of kFew threads,
 // several in a wavefront, also where more threads per element were asked for:
 // the others would have nothing to do, and the sums, whose butterfly skips the
-// levels without particles, are the same.
+// levels without particles, are the same to rounding.
 // Q1 only: of the 109 outputs of a Q2 element each thread of so small a group
 // stores seven, which takes longer than the particles (the fluidized Q2 bed
 // with some such elements at its surface would go from 14.7 to 17.5 us).  And
-// only where there are enough of them, for a group's chain is the longer one.
-// A suspension of 150k particles, 9 in each element (Q1, FP64): 81.3 -> 35.1 us.
+// only where there are kFewMin of them (fewer fit the chip at once, a block
+// each, and a group's chain is the longer one), of at most kFewCells cells (a
+// group reads 16 counts at a time).  Coupling calls of FP64 beds filled with
+// elements of nine particles, 128 threads, with a block for each element and
+// with groups: 28 and 18 us for 2,744 elements, 80 and 22 for 8,000, 129 and 33
+// for 13,824; of 2,744 elements of 2,744 cells and 16 particles: groups 206 us,
+// blocks 114.
 constexpr int kFew = 16;
 constexpr int kFewMin = 2048;
-static bool splits_few(int order, int nt) { return order == 1 && nt != 16 && nt != 32; }
+constexpr int kFewCells = 1024;
+// Whether a mesh is classified by the number of particles at all.  Where there
+// can be no kFewMin such elements, or most elements hold more (the mean over
+// the mesh is above kFew), the pass and the larger kernel only cost (1,331
+// elements of nine particles, FP64: 25 us against 17).  Elements of more cells
+// than the block has threads take the larger kernel in any case, whose loop
+// over the cells' counts is the faster one (1,331 elements of 1,000 cells: 60
+// -> 38 us).
+static bool splits_few(int order, int nt, long long n, long long ne, int kk) {
+  return order == 1 && nt != 16 && nt != 32 && (kk > 128 || (ne >= kFewMin && n <= kFew * ne));
+}
 // tot with min(m, kFew + 1) more in the half at `shift` (at most 64 lanes are
 // added up later), which stays at most kFew + 1.
 __device__ inline unsigned min_few(unsigned tot, int m, int shift) {
@@ -974,13 +989,10 @@ __global__ __launch_bounds__(block_threads<NT>(), occ_waves<MODE>()) void couple
   const int g = (int)threadIdx.x / NT;
   const int first = (int)blockIdx.x * kG + g;
   const int last = D.grid.n_elem - 1;
-  // parity < 0: every element, in order.  Otherwise the list entry is read in
-  // the same round trip as the list length (the list has n_elem entries)
-  int nocc = last + 1, e = first;
-  if (parity >= 0) {
-    nocc = min(D.err[kOccWord + parity], nocc);
-    e = D.occ[first < last ? first : last];
-  }
+  // the list entry is read in the same round trip as the list length (the
+  // list has n_elem entries)
+  const int nocc = min(D.err[kOccWord + parity], D.grid.n_elem);
+  const int e = D.occ[first < last ? first : last];
   __asm__ volatile("" ::: "memory");
   if ((int)blockIdx.x * kG >= nocc) return;  // whole block
   const int tid = threadIdx.x;
@@ -992,9 +1004,32 @@ __global__ __launch_bounds__(block_threads<NT>(), occ_waves<MODE>()) void couple
     couple_element<R, ORD, MODE, NT>(D, C, D.occ[i], U, P, eps_q, beta_q, fpf_q, esums, p2, p3, sh[g], sLq);
 }
 
-// The same with the elements of few particles apart: crowded ones, from the
-// end of the list, by the whole block, then the others (in groups, when there
-// are kFewMin of them).
+// The same for every element of a mesh of few, in order, without a list.  A
+// kernel of its own: as a case of the one above, decided at run time, it cost
+// the listed elements' variants that spill two more waits for spilled
+// registers at their start (1,728 elements, FP64, 128 threads: 24 -> 28 us).
+template <typename R, int ORD, int MODE, int NT>
+__global__ __launch_bounds__(block_threads<NT>(), occ_waves<MODE>()) void couple_all(
+    Dev D, Cpl C, int p2, int p3, const double *__restrict__ U, const double *__restrict__ P,
+    double *__restrict__ eps_q, double *__restrict__ beta_q, double *__restrict__ fpf_q,
+    double *__restrict__ esums) {
+  constexpr int kG = elems_per_block<NT>();
+  __shared__ CplShared<NT> sh[kG];
+  __shared__ double sLq[3][3];  // 1D velocity basis at the Gauss points
+  const int g = (int)threadIdx.x / NT;
+  const int e = (int)blockIdx.x * kG + g;
+  const int tid = threadIdx.x;
+  if (tid < 9) sLq[tid / 3][tid % 3] = C.Lq[tid / 3][tid % 3];  // read after the element's first barrier
+  if (e >= D.grid.n_elem) return;  // whole group (a group of a wavefront: no block barrier follows)
+  couple_element<R, ORD, MODE, NT>(D, C, e, U, P, eps_q, beta_q, fpf_q, esums, p2, p3, sh[g], sLq);
+}
+
+// The same with the elements of few particles listed apart, from the front of
+// the list, and the crowded ones from its end: both a block for each element
+// or, where groups are taken for the former, the crowded ones first.  A block's
+// first element stands outside the loop, for a loop makes the compiler hold the
+// closure's constants across the element (crowded FP64 beds of 4,096 elements
+// took 57 us in one loop, 42 so; 39 in couple_occupied).
 template <typename R, int ORD, int MODE, int NT>
 __global__ __launch_bounds__(block_threads<NT>(), occ_waves<MODE>()) void couple_occupied_few(
     Dev D, Cpl C, int p2, int p3, int parity, const double *__restrict__ U, const double *__restrict__ P,
@@ -1010,18 +1045,24 @@ __global__ __launch_bounds__(block_threads<NT>(), occ_waves<MODE>()) void couple
   const int last = D.grid.n_elem - 1;
   const int nfew = min(D.err[kOccWord + parity], last + 1);
   const int ncrowd = min(D.err[kOccWord + 2 + parity], last + 1 - nfew);
-  const int e0 = D.occ[last - min(first, last)];
+  const int at = min(first, last);  // the block's entries from either end, in the same round trip
+  const int front = D.occ[at], back = D.occ[last - at];
   __asm__ volatile("" ::: "memory");
   if (first >= ncrowd + nfew) return;  // whole block
   const int tid = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   if (tid < 9) sLq[wave][tid / 3][tid % 3] = C.Lq[tid / 3][tid % 3];  // read after the element's first barrier
-  const int whole = ncrowd + (nfew < kFewMin ? nfew : 0);
+  const bool grouped = nfew >= kFewMin && D.grid.kk <= kFewCells;
+  const int nf = grouped ? 0 : nfew;  // elements of few particles computed by whole blocks
+  const int whole = nf + ncrowd;
   int i = first;
-  for (; i < whole; i += (int)gridDim.x) {
-    const int e = i == first && i < ncrowd ? e0 : D.occ[i < ncrowd ? last - i : i - ncrowd];
+  if (i < whole) {  // the first element outside the loop, as above
+    const int e = i < nf ? front : (nf ? D.occ[last - (i - nf)] : back);
     couple_element<R, ORD, MODE, NT>(D, C, e, U, P, eps_q, beta_q, fpf_q, esums, p2, p3, u.sh, sLq[wave]);
+    for (i += (int)gridDim.x; i < whole; i += (int)gridDim.x)
+      couple_element<R, ORD, MODE, NT>(D, C, D.occ[i < nf ? i : last - (i - nf)], U, P, eps_q, beta_q, fpf_q, esums,
+                                       p2, p3, u.sh, sLq[wave]);
   }
-  if (nfew < kFewMin) return;
+  if (!grouped) return;
   // no block barrier from here on
   const int g = (int)threadIdx.x / kFew;
   for (int k = (i - whole) * kGroups + g; k < nfew; k += (int)gridDim.x * kGroups)
@@ -1202,11 +1243,17 @@ hipError_t launch_couple(const Dev &D, const Cpl &C, long long s, long long call
                          double *esums, bool fp32, hipStream_t st) {
   const int p2 = (int)(s & 1), p3 = (int)(s % 3);
   const int ne = D.grid.n_elem;
-  const int parity = couples_all(ne, C.elem_threads) ? -1 : (int)(call & 1);
+  const int parity = (int)(call & 1);
   const int waves_c = (ne + kClassElems - 1) / kClassElems;
   const int grid_c = (waves_c + kClassBlock / kWave - 1) / (kClassBlock / kWave);
   const int mode = cpl_mode_of(C.drag, C.shear || C.smooth);
-  if (parity >= 0 && splits_few(C.order, C.elem_threads)) {
+  if (couples_all(ne, C.elem_threads)) {
+    CFDDEM_DISPATCH((couple_all<RT_, O_, M_, NT_><<<occ_grid<NT_>(ne), block_threads<NT_>(), 0, st>>>(
+                        D, C, p2, p3, U, P, eps_q, beta_q, fpf_q, esums)),
+                    fp32, C.order, mode, C.elem_threads);
+    return hipGetLastError();
+  }
+  if (splits_few(C.order, C.elem_threads, D.n, ne, D.grid.kk)) {
     couple_classify<true><<<grid_c, kClassBlock, 0, st>>>(D, C, p3, parity, eps_q, beta_q, fpf_q, esums);
 #define CFDDEM_FEW(R, M)                                                                                        \
   do {                                                                                                          \
@@ -1229,7 +1276,7 @@ hipError_t launch_couple(const Dev &D, const Cpl &C, long long s, long long call
 #undef CFDDEM_FEW
     return hipGetLastError();
   }
-  if (parity >= 0) couple_classify<false><<<grid_c, kClassBlock, 0, st>>>(D, C, p3, parity, eps_q, beta_q, fpf_q, esums);
+  couple_classify<false><<<grid_c, kClassBlock, 0, st>>>(D, C, p3, parity, eps_q, beta_q, fpf_q, esums);
   CFDDEM_DISPATCH((couple_occupied<RT_, O_, M_, NT_><<<occ_grid<NT_>(ne), block_threads<NT_>(), 0, st>>>(
                       D, C, p2, p3, parity, U, P, eps_q, beta_q, fpf_q, esums)),
                   fp32, C.order, mode, C.elem_threads);
