@@ -250,8 +250,8 @@ __device__ inline void basis1d_deriv(int order, double t, double d1[3], double d
 // element whose nodal velocities are sU:
 //   div tau = mu_f (lap u + grad(div u) / 3),
 // from the second derivatives of the Q_n field, sum-factorized axis by axis.
-template <int ORD>
-__device__ inline void div_tau(const double xi[3], const double (*sU)[27], const double inv_he[3],
+template <int ORD, typename Inv>
+__device__ inline void div_tau(const double xi[3], const double (*sU)[27], const Inv &inv_he,
                                double mu_f, double out[3]) {
   constexpr int p1 = ORD + 1;
   double V[3][3], D1[3][3], D2[3][3];
@@ -336,13 +336,14 @@ __device__ inline R difelice_beta(R rho_f, R mu_f, R eps, R d, R slip, unsigned 
 
 // Per-particle step 3 of one element: interpolation, closure, f_fp, and the
 // thread's running element sums.
-template <typename R, int ORD, int MODE>
-__device__ inline void particle_force(const Dev &D, const Cpl &C, int k, const int ee[3],
+// D, C: const Dev and const Cpl, or cDev and cCpl.
+template <typename R, int ORD, int MODE, typename DevRef, typename CplRef>
+__device__ inline void particle_force(DevRef &D, CplRef &C, int k, const int ee[3],
                                       const double xp[3], const double up[3], double r,
                                       double eps_c, const double (*sU)[27], const double *sP,
                                       const double *sE,
                                       double sums[10]) {
-  const Grid &G = D.grid;
+  auto &G = D.grid;
   const int n = D.n;
   constexpr int p1 = ORD + 1;
   double xi[3];
@@ -527,8 +528,8 @@ __device__ inline void cpl_sync() {
 // handled by thread t mod NT.  The latency is a short chain of memory round
 // trips: counts, slot entries and nodal values are loaded together, then the
 // particles' state, then the outputs are stored.
-template <typename R, int ORD, int MODE, int NT>
-__device__ __forceinline__ void couple_element(const Dev &D, const Cpl &C, int e, const double *__restrict__ U,
+template <typename R, int ORD, int MODE, int NT, typename DevRef, typename CplRef>
+__device__ __forceinline__ void couple_element(DevRef &D, CplRef &C, int e, const double *__restrict__ U,
                                const double *__restrict__ P, double *__restrict__ eps_q,
                                double *__restrict__ beta_q, double *__restrict__ fpf_q,
                                double *__restrict__ esums, int p2, int p3, CplShared<NT> &sh,
@@ -536,7 +537,7 @@ __device__ __forceinline__ void couple_element(const Dev &D, const Cpl &C, int e
   constexpr int kCplThreads = NT;
   constexpr int kCplWaves = elem_waves<NT>();
   constexpr int GW = NT < kWave ? NT : kWave;  // lanes of this element in one wavefront
-  const Grid &G = D.grid;
+  auto &G = D.grid;
   const int n = D.n;
   const int tid = threadIdx.x & (NT - 1);
   const int lane = tid & (GW - 1);
@@ -1024,6 +1025,14 @@ __global__ __launch_bounds__(block_threads<NT>(), occ_waves<MODE>()) void couple
   couple_element<R, ORD, MODE, NT>(D, C, e, U, P, eps_q, beta_q, fpf_q, esums, p2, p3, sh[g], sLq);
 }
 
+// Two wavefronts per SIMD for every FP64 variant of the kernel below: at three
+// (168 registers) the one for Di Felice alone spilled 98 and took 240 bytes of
+// scratch memory per lane, at two it needs 233 and none.
+template <typename R, int MODE>
+constexpr int few_waves() {
+  return sizeof(R) == 8 ? 2 : occ_waves<MODE>();
+}
+
 // The same with the elements of few particles listed apart, from the front of
 // the list, and the crowded ones from its end: both a block for each element
 // or, where groups are taken for the former, the crowded ones first.  A block's
@@ -1031,10 +1040,12 @@ __global__ __launch_bounds__(block_threads<NT>(), occ_waves<MODE>()) void couple
 // closure's constants across the element (crowded FP64 beds of 4,096 elements
 // took 57 us in one loop, 42 so; 39 in couple_occupied).
 template <typename R, int ORD, int MODE, int NT>
-__global__ __launch_bounds__(block_threads<NT>(), occ_waves<MODE>()) void couple_occupied_few(
-    Dev D, Cpl C, int p2, int p3, int parity, const double *__restrict__ U, const double *__restrict__ P,
+__global__ __launch_bounds__(block_threads<NT>(), (few_waves<R, MODE>())) void couple_occupied_few(
+    Dev, Cpl, int p2, int p3, int parity, const double *__restrict__ U, const double *__restrict__ P,
     double *__restrict__ eps_q, double *__restrict__ beta_q, double *__restrict__ fpf_q,
     double *__restrict__ esums) {
+  cDev &D = args_dev();
+  cCpl &C = args_cpl();
   constexpr int kGroups = NT / kFew;  // elements of few particles a block takes at once
   __shared__ union {
     CplShared<NT> sh;

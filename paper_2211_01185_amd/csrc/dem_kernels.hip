@@ -35,9 +35,6 @@
 
 namespace cfddem {
 
-// The Dev that is the first argument of the running kernel.
-__device__ __forceinline__ cDev &args_dev() { return *(cDev *)__builtin_amdgcn_kernarg_segment_ptr(); }
-
 // Binning of x into the grid of a step (counts cnt, slots sl, cells cl) and
 // the displacement test against the last broad-search positions.  In a grid
 // that is not exact, a particle in its home cell (home_k) takes no slot.
@@ -874,9 +871,10 @@ __device__ inline int xcd_run_block(int i, int nb, int C) {
 
 // Wavefronts per SIMD that the force kernels leave registers for.  Four are
 // 128 registers, which holds every FP32 variant and the plain FP64 one; with
-// rolling friction, or over a batch's table, the FP64 kernel needs up to 23
+// rolling friction, or over a batch's table, the FP64 kernel needs up to 14
 // more.  It gets them: held in scratch memory instead they cost time on every
-// step, and a build that did so gave results that differed from run to run.
+// step, and a build that did so gave results that differed from run to run (the
+// reason was not found, so the build refuses such a kernel).
 template <typename R, bool ROLL, bool BATCH>
 constexpr int force_waves() {
   return sizeof(R) == 8 && (ROLL || BATCH) ? 3 : 4;

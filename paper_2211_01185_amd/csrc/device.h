@@ -201,6 +201,13 @@ __device__ __forceinline__ gptr<T> glb(T *p) {
 // a batch table): its fields come by scalar loads where they are used, instead
 // of all of them being held in registers from the start of the kernel.
 typedef const __attribute__((address_space(4))) Dev cDev;
+typedef const __attribute__((address_space(4))) Cpl cCpl;
+
+// The Dev, and the Cpl after it, that are the first arguments of the running
+// kernel.
+__device__ __forceinline__ cDev &args_dev() { return *(cDev *)__builtin_amdgcn_kernarg_segment_ptr(); }
+static_assert(sizeof(Dev) % alignof(Cpl) == 0, "Cpl follows Dev in the argument segment");
+__device__ __forceinline__ cCpl &args_cpl() { return *(cCpl *)(&args_dev() + 1); }
 
 // Buffer i of a double- or triple-buffered array, with constant indices only
 // (so that a Dev copied into registers stays in registers).

@@ -96,3 +96,43 @@ def test_full_lists_shared_by_more_lanes(n_side, precision):
             compare_contacts(gb, ob, tol)
             compare_states(gb, ob, tol, keys=("x", "v", "w", "Fc", "Tc"))
         assert gb.poll()[0] == 0
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("mu_r", [0.0, 0.1])
+@pytest.mark.parametrize("n_side", [(16, 16, 31), (35, 35, 34)])  # four lanes to a list's part, and one
+def test_every_share_of_a_list_has_the_same_bits_each_time(n_side, mu_r, precision):
+    wl = _moving_lattice(n_side, mu_r)
+    runs = []
+    for _ in range(2):
+        gb = gpu_bed(wl, precision, resort_every=7, skin=1e-5)
+        gb.step(20)
+        runs.append((gpu_state(gb), gb.read_contacts()))
+        assert gb.poll()[0] == 0
+    (a, ca), (b, cb) = runs
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
+    for p, q in zip(ca, cb):
+        assert np.array_equal(p, q)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("lanes", [1, 2, 4])
+def test_batches_have_the_same_bits_each_time(lanes, precision):
+    """A bed with rolling friction and one without (a kernel for each), large
+    enough to fill the chip."""
+    runs = []
+    for _ in range(2):
+        beds = [gpu_bed(_moving_lattice((32, 32, 32), mu_r), precision, lanes=lanes, resort_every=7, skin=1e-5)
+                for mu_r in (0.0, 0.1)]
+        batch = cfddem.Batch(beds)
+        for _ in range(4):
+            batch.step(5)
+        runs.append([(gpu_state(b), b.read_contacts()) for b in beds])
+        assert all(b.poll()[0] == 0 for b in beds)
+        batch.close()
+    for (a, ca), (b, cb) in zip(*runs):
+        for k in a:
+            assert np.array_equal(a[k], b[k]), k
+        for p, q in zip(ca, cb):
+            assert np.array_equal(p, q)
