@@ -52,11 +52,19 @@ def _scale(d, counter):
     return COPY_KIB / (sum(big) / len(big)), len(big)
 
 
+def force_kernel_names(lanes):
+    """Patterns of the single-bed contact-force kernels (FP32 forces, no rolling
+    friction, any number of lanes sharing a list's part): the creation-time
+    evaluation and the steps."""
+    tail = rf"{lanes}, false, \d+>"
+    return (re.compile(rf"force_kick<float, false, false, {tail}"),
+            re.compile(rf"force_kick<float, true, (true|false), {tail}"))
+
+
 def _region(d, counter, lanes, warmup, steps):
     """Counter values of the force-kernel step launches of the last bed the
     run created (the replayed region), after its warm-up."""
-    step_re = re.compile(rf"force_kick<float, true, (true|false), {lanes}, false>")
-    prime_re = re.compile(rf"force_kick<float, false, false, {lanes}, false>")
+    prime_re, step_re = force_kernel_names(lanes)
     rows = [r for r in _rows(d) if r["Counter_Name"] == counter]
     last_prime = max(i for i, r in enumerate(rows) if prime_re.search(r["Kernel_Name"]))
     launches = [r for r in rows[last_prime + 1:] if step_re.search(r["Kernel_Name"])]

@@ -11,7 +11,7 @@ of the spouted-bed measurement's timed bed instead (the last two beds created
 at that bed's grid are the timed one and its replay; the tuner's trial beds
 come before them).  A bed of the main measurement is
 recognised by its creation-time evaluation (force_kick<float, false, false,
-L, false>: no rolling friction) at the main bed's grid size followed by step
+L, false, S>: no rolling friction) at the main bed's grid size followed by step
 launches of the single-bed kernel; the timed bed runs exactly warm-up + timed
 steps and the window's beds the window's steps (the autotuner's trials run two
 more coupling periods, the settling run thousands of steps, the smoothing run
@@ -32,6 +32,7 @@ import re
 
 import numpy as np
 
+from .pmc_summary import force_kernel_names
 
 
 def _force_block():
@@ -81,8 +82,7 @@ def main(argv=None):
     rows = _one(args.trace, "kernel_trace.csv")
     key = "Kernel_Name" if "Kernel_Name" in rows[0] else "Name"
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
-    prime_re = re.compile(rf"cfddem::force_kick<float, false, false, {lanes}, false, \d>")
-    step_re = re.compile(rf"cfddem::force_kick<float, true, (true|false), {lanes}, false, \d>")
+    prime_re, step_re = force_kernel_names(lanes)
     beds, cur = [], None
     for r in rows:
         if int(r.get("Grid_Size", r.get("Grid_Size_X", 0)) or 0) != grid:
@@ -128,8 +128,7 @@ def spouted(args, bench):
     key = "Kernel_Name" if "Kernel_Name" in rows[0] else "Name"
     gkey = "Grid_Size" if "Grid_Size" in rows[0] else "Grid_Size_X"
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
-    prime_re = re.compile(rf"cfddem::force_kick<float, false, false, {lanes}, false, \d>")
-    step_re = re.compile(rf"cfddem::force_kick<float, true, (true|false), {lanes}, false, \d>")
+    prime_re, step_re = force_kernel_names(lanes)
     starts = [i for i, r in enumerate(rows) if int(r[gkey] or 0) == grid and prime_re.search(r[key])]
     starts.append(len(rows))
     # the timed bed: the first bed at this grid that runs exactly warm-up +
