@@ -200,7 +200,9 @@ __device__ inline void contact_law(const Mat &M, const double n[3], double dn,
     vrt[c] = vij[c] - vrn[c];
   }
   if (ADVANCE) {
-    const double along = dto[0] * n[0] + dto[1] * n[1] + dto[2] * n[2];
+    // the products in this order, written out: left to the compiler, the first
+    // one rounded was another one where lanes share a list
+    const double along = fma(dto[2], n[2], fma(dto[1], n[1], dto[0] * n[0]));
     for (int c = 0; c < 3; ++c) dtn[c] = (dto[c] - along * n[c]) + vrt[c] * dt;
   } else {
     for (int c = 0; c < 3; ++c) dtn[c] = 0.0;

@@ -136,3 +136,55 @@ def test_batches_have_the_same_bits_each_time(lanes, precision):
             assert np.array_equal(a[k], b[k]), k
         for p, q in zip(ca, cb):
             assert np.array_equal(p, q)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("mu_r", [0.0, 0.1])
+def test_a_part_of_a_list_has_the_same_sum_for_any_number_of_lanes(mu_r, precision):
+    """The same touching spheres, alone (four lanes), and with others at rest
+    beside them that make the bed large enough for two lanes and for one."""
+    wl = _moving_lattice((12, 11, 13), mu_r)
+    wl.dem["gravity"] = [0.0, 0.0, 0.0]
+    n, d, top = wl.n, 2.0 * float(wl.radius[0]), float(wl.dem["box_hi"][2])
+    wl.dem["box_hi"] = [0.15, 0.15, 0.25]
+    wl.fluid["n_el"] = [10, 10, 16]
+    k = np.arange(41000)
+    rest = np.stack([(1 + k % 36) * 1.3 * d, (1 + k // 36 % 36) * 1.3 * d, top + (1 + k // 1296) * 1.3 * d])
+    runs = []
+    for extra in (0, 20000, 41000):
+        one = synth.lattice(n_side=(2, 2, 2))
+        one.dem, one.fluid = wl.dem, wl.fluid
+        one.x = np.concatenate([wl.x, rest[:, :extra]], 1)
+        one.v = np.concatenate([wl.v, np.zeros((3, extra))], 1)
+        one.w = np.concatenate([wl.w, np.zeros((3, extra))], 1)
+        one.radius, one.density = np.full(n + extra, 0.5 * d), np.full(n + extra, 2500.0)
+        gb = gpu_bed(one, precision, skin=1e-5, resort_every=7)
+        gb.step(10)
+        assert gb.poll()[0] == 0
+        st = {key: v[:, :n] for key, v in gpu_state(gb).items()}
+        runs.append((st, gb.read_contacts()))
+    for st, contacts in runs[1:]:
+        for key in st:
+            assert np.array_equal(st[key], runs[0][0][key]), key
+        for p, q in zip(contacts, runs[0][1]):
+            assert np.array_equal(p, q)
+    assert len(runs[0][1][0]) > 2000
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("mu_r", [0.0, 0.1])
+@pytest.mark.parametrize("lanes", [1, 2, 4])
+@pytest.mark.parametrize("n_side", [(16, 16, 20), (24, 24, 30), (36, 36, 36)])
+def test_a_batch_of_one_has_the_bits_of_the_bed_alone(n_side, lanes, mu_r, precision):
+    wl = _moving_lattice(n_side, mu_r)
+    alone, other = (gpu_bed(wl, precision, lanes=lanes, resort_every=7, skin=1e-5) for _ in range(2))
+    batch = cfddem.Batch([other])
+    alone.step(10)
+    batch.step(10)
+    a, b = gpu_state(alone), gpu_state(other)
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
+    for p, q in zip(alone.read_contacts(), other.read_contacts()):
+        assert np.array_equal(p, q)
+    assert alone.poll()[0] == 0 and other.poll()[0] == 0
+    batch.close()
