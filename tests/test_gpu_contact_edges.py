@@ -110,3 +110,29 @@ def test_infinite_and_overflowing_quotients(precision):
             assert np.array_equal(w, torque / inertia)
         assert np.max(np.abs(v)) == 0.0
         assert gb.poll()[0] == 0
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_quotients_of_the_kicks(precision):
+    """Newton steps against the division: the same bits over the exponent
+    range, masses with every mantissa bit set among them; one unit in the last
+    place where such a mass divides a power of two (the exception of a residual
+    step after a reciprocal rounded to nearest)."""
+    rng = np.random.default_rng(11)
+
+    def numbers(lo, hi, size):
+        return rng.choice([-1.0, 1.0], size) * rng.uniform(1.0, 2.0, size) * 2.0 ** rng.integers(lo, hi, size)
+
+    ones = np.arange(1000) % 4 == 0
+    mass = np.abs(numbers(-60, 20, 1000))
+    mass[ones] = (2.0 - 2.0 ** -52) * 2.0 ** rng.integers(-60, 20, int(ones.sum()))
+    force, torque = numbers(-400, -60, (3, 1000)), numbers(-400, 0, (3, 1000))  # no sphere reaches another
+    force[0, ::3] = 0.0
+    power = np.zeros((3, 1000), dtype=bool)
+    power[2, ::8] = True
+    force[2, ::8] = 2.0 ** rng.integers(-400, -60, 125)
+    v, w, inertia, _ = _kicked(precision, force, torque, mass)
+    assert np.array_equal(w, torque / inertia)
+    want = force / mass
+    assert np.array_equal(v[~power], want[~power])
+    assert np.max(np.abs(v[power] / want[power] - 1.0)) <= 2.0 ** -52
