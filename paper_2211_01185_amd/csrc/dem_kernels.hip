@@ -69,10 +69,10 @@ __device__ inline void bin_and_test(cDev &D, int k, const double xp[3], const do
 // form for the root) and end with a step on the exact residual.  That rounds
 // as `sqrt` and `/` do wherever it was compared (10^9 random arguments of
 // exponents -40 to 19; in the kicks numerators down to 2^-400), but for the
-// reciprocal of an x whose mantissa bits are all ones, which is half a unit in
-// the last place from two neighbours and comes out as the other one.  Arguments
-// are normal numbers with normal reciprocals; roots near the ends of the
-// exponent range go to the library.  Coupled runs of 100k packed spheres, FP32
+// reciprocal of an x whose mantissa bits are all ones: it lies all but in the
+// middle between two numbers and comes out as the farther one.  Arguments are
+// normal numbers with normal reciprocals; roots near the ends of the exponent
+// range go to the library.  Coupled runs of 100k packed spheres, FP32
 // forces: 34.7 -> 30.2 us per DEM step; the fluidized bed 31.7 -> 27.4.
 __device__ __forceinline__ double recip(double x) {  // 1 / x, x > 0 and normal
   double y = __builtin_amdgcn_rcp(x);
@@ -84,11 +84,12 @@ __device__ __forceinline__ double quot(double a, double x, double inv) {  // a /
   const double q = a * inv;
   return fma(-fma(q, x, -a), inv, q);  // this sign of the residual keeps a zero's
 }
-// The same for any a: a quotient that is not finite, whose residual would be a
-// NaN, is left as it is.
-__device__ __forceinline__ double quot_any(double a, double x, double inv) {
-  const double q = a * inv, r = fma(-fma(q, x, -a), inv, q);
-  return fabs(q) < __builtin_inf() ? r : q;
+// Three of them for any a: the hardware's last step of a division puts right an
+// infinite quotient, whose residual is a NaN (one instruction for each; a test
+// of the quotients with selects took 0.7 % of a packed bed's step, a branch 1 %).
+__device__ __forceinline__ void quot_any(const double a[3], double x, double out[3]) {
+  const double inv = recip(x);
+  for (int c = 0; c < 3; ++c) out[c] = __builtin_amdgcn_div_fixup(quot(a[c], x, inv), x, a[c]);
 }
 __device__ __forceinline__ double root(double x, double &inv) {  // sqrt(x), inv: its reciprocal within 2 ulp
   const double y = __builtin_amdgcn_rsq(x);
@@ -136,14 +137,19 @@ __device__ __forceinline__ void drift_bin_body(cDev &D, int k, int p2, int p3, i
     const dvec4 xo = gsel(D.pr, p2 ^ 1)[k];
     const double x0[3] = {xo.x, xo.y, xo.z};
     const double inertia = 0.4 * m * r * r;
-    const double im = recip(m), ii = recip(inertia);
-    double vhc[3], whc[3];
+    double f[3], t[3], acc[3], alpha[3], vhc[3], whc[3];
     for (int c = 0; c < 3; ++c) {
       const int i = c * n + k;
-      const double acc = quot_any(glb(D.Fc)[i] + glb(D.ffp)[i], m, im) + D.g[c];
-      const double alpha = quot_any(glb(D.Tc)[i], inertia, ii);
-      vhc[c] = glb(D.v)[i] + 0.5 * D.dt * acc;
-      whc[c] = glb(D.w)[i] + 0.5 * D.dt * alpha;
+      f[c] = glb(D.Fc)[i] + glb(D.ffp)[i];
+      t[c] = glb(D.Tc)[i];
+    }
+    quot_any(f, m, acc);
+    quot_any(t, inertia, alpha);
+    for (int c = 0; c < 3; ++c) {
+      const int i = c * n + k;
+      acc[c] += D.g[c];
+      vhc[c] = glb(D.v)[i] + 0.5 * D.dt * acc[c];
+      whc[c] = glb(D.w)[i] + 0.5 * D.dt * alpha[c];
       xp[c] = x0[c] + D.dt * vhc[c];
     }
     x1[k] = dvec4{xp[0], xp[1], xp[2], r};
@@ -809,12 +815,13 @@ __device__ __forceinline__ void force_kick_body(cDev &D, int blk, int p2, int p3
     const double xbl[3] = {glb(D.xb)[a], glb(D.xb)[n + a], glb(D.xb)[2 * n + a]};
     const double xba[3] = {rebuild ? xa0 : xbl[0], rebuild ? xa1 : xbl[1], rebuild ? xa2 : xbl[2]};
     const double inertia = 0.4 * ma * ra * ra;
-    const double im = recip(ma), ii = recip(inertia);
-    double vb[3], wb[3], acc[3], alpha[3];
+    double f[3], vb[3], wb[3], acc[3], alpha[3];
+    for (int c = 0; c < 3; ++c) f[c] = F[c] + fa[c];
+    quot_any(f, ma, acc);
+    quot_any(T, inertia, alpha);
     for (int c = 0; c < 3; ++c) {
       const int i = c * n + a;
-      acc[c] = quot_any(F[c] + fa[c], ma, im) + D.g[c];
-      alpha[c] = quot_any(T[c], inertia, ii);
+      acc[c] += D.g[c];
       vb[c] = (c == 0 ? va0 : (c == 1 ? va1 : va2)) + 0.5 * D.dt * acc[c];
       wb[c] = (c == 0 ? wa0 : (c == 1 ? wa1 : wa2)) + 0.5 * D.dt * alpha[c];
       if (!CONT) {
