@@ -534,7 +534,7 @@ __device__ __forceinline__ Entry load_entry(gptr<const dvec4> P, gptr<const dvec
 
 // ROLL: some rolling friction coefficient is nonzero (a separate
 // instantiation, so that the kernels without it keep their registers).
-template <typename R, bool ADVANCE, bool CONT, int V, bool ROLL, int S>
+template <typename R, bool ADVANCE, bool CONT, int V, bool ROLL, int S, bool BATCH>
 __device__ __forceinline__ void force_kick_body(cDev &D, int blk, int p2, int p3, const int *src, int gmode) {
   constexpr int L = V * S;  // lanes of a particle
   const int gid = blk * kForceBlock + threadIdx.x;
@@ -814,6 +814,9 @@ __device__ __forceinline__ void force_kick_body(cDev &D, int blk, int p2, int p3
     const double fa[3] = {glb(D.ffp)[a], glb(D.ffp)[n + a], glb(D.ffp)[2 * n + a]};
     const double xbl[3] = {glb(D.xb)[a], glb(D.xb)[n + a], glb(D.xb)[2 * n + a]};
     const double xba[3] = {rebuild ? xa0 : xbl[0], rebuild ? xa1 : xbl[1], rebuild ? xa2 : xbl[2]};
+    // keeps the tail's stores below these loads (this kernel would need a
+    // register more than it has)
+    if constexpr (BATCH && sizeof(R) == 8) __asm__ __volatile__("" ::: "memory");
     const double inertia = 0.4 * ma * ra * ra;
     double f[3], vb[3], wb[3], acc[3], alpha[3];
     for (int c = 0; c < 3; ++c) f[c] = F[c] + fa[c];
@@ -882,19 +885,19 @@ __device__ inline int xcd_run_block(int i, int nb, int C) {
 }
 
 // Wavefronts per SIMD that the force kernels leave registers for.  Four are
-// 128 registers, which holds every FP32 variant and the plain FP64 one; with
-// rolling friction, or over a batch's table, the FP64 kernel needs up to 14
-// more.  It gets them: held in scratch memory instead they cost time on every
+// 128 registers, which holds every FP32 variant and the plain FP64 ones; with
+// rolling friction, or with four lanes over a batch's table, the FP64 kernel
+// needs up to 14 more.  It gets them: held in scratch memory instead they cost time on every
 // step, and a build that did so gave results that differed from run to run (the
 // reason was not found, so the build refuses such a kernel).
-template <typename R, bool ROLL, bool BATCH>
+template <typename R, bool ROLL, bool BATCH, int L>
 constexpr int force_waves() {
-  return sizeof(R) == 8 && (ROLL || BATCH) ? 3 : 4;
+  return sizeof(R) == 8 && (ROLL || (BATCH && L == 4)) ? 3 : 4;
 }
 
 template <typename R, bool ADVANCE, bool CONT, int L, bool ROLL, int S>
-__global__ __launch_bounds__(kForceBlock, (force_waves<R, ROLL, false>())) void force_kick(Dev D, int p2, int p3, const int *src, int gmode) {
-  force_kick_body<R, ADVANCE, CONT, L, ROLL, S>(args_dev(), xcd_block(blockIdx.x, gridDim.x), p2, p3, src, gmode);
+__global__ __launch_bounds__(kForceBlock, (force_waves<R, ROLL, false, L>())) void force_kick(Dev D, int p2, int p3, const int *src, int gmode) {
+  force_kick_body<R, ADVANCE, CONT, L, ROLL, S, false>(args_dev(), xcd_block(blockIdx.x, gridDim.x), p2, p3, src, gmode);
 }
 
 // ---------------------------------------------------------------------------
@@ -927,7 +930,7 @@ __global__ __launch_bounds__(256) void drift_bin_batch(const Dev *__restrict__ t
 // Step run.s + i of every bed, of a run of n steps (i = 1 applies the bed's
 // pending permutation).
 template <typename R, bool CONT, int L, bool ROLL>
-__global__ __launch_bounds__(kForceBlock, (force_waves<R, ROLL, true>())) void force_kick_batch(const Dev *__restrict__ tab,
+__global__ __launch_bounds__(kForceBlock, (force_waves<R, ROLL, true, L>())) void force_kick_batch(const Dev *__restrict__ tab,
                                                                    const BedRun *__restrict__ run,
                                                                    const unsigned *__restrict__ map,
                                                                    int i, int n) {
@@ -935,7 +938,7 @@ __global__ __launch_bounds__(kForceBlock, (force_waves<R, ROLL, true>())) void f
   const int b = (int)(m >> kBedShift), blk = (int)(m & kBlockMask);
   cDev &D = ((cDev *)tab)[b];
   const long long s = run[b].s + i;
-  force_kick_body<R, true, CONT, L, ROLL, 1>(D, blk, (int)(s & 1), (int)(s % 3),
+  force_kick_body<R, true, CONT, L, ROLL, 1, true>(D, blk, (int)(s & 1), (int)(s % 3),
                                           i == 1 ? run[b].src : nullptr, grid_mode(i, n));
 }
 
