@@ -1089,15 +1089,24 @@ static void launch_fk_lanes(const Dev &D, int p2, int p3, const int *src, int gm
 // contacts of a part side by side and add them up in the list's order, so that
 // the result has the same bits for any number of them.  That shortens the
 // chain of a wavefront (one contact after the other, which is what a small bed
-// waits for) and takes as many more wavefronts: it pays until they fill the
-// SIMDs.  One, two and four lanes, us per step: 1,000 particles FP64 10.2, 8.7,
-// 8.0; 20k FP32 9.0, 8.6, 9.3; 37k FP64 with rolling friction 17.5, 16.2, 19.7;
-// 100k FP32 21.6, 23, 28.  Hence four while that is one wavefront per SIMD and
-// two up to two and a half.  A batch fills the chip with its beds and takes one.
+// waits for) and takes as many more wavefronts, which a bed without contacts
+// pays for in vain.  One, two and four lanes, us per step, of dense beds
+// (spacing 0.998 d), loose ones (1.094 d), ones without a contact (1.3 d):
+//   4,000   9.9  8.9  8.0 |  8.5  7.6  7.5 | 6.8  6.7  7.0
+//   8,100  10.6  9.6  9.0 |  8.7  8.1  8.2 | 6.9  7.1  7.6
+//  16,000  11.3 10.4 10.3 |  9.2  8.5  9.0 | 7.2  7.2  8.0
+//  20,000  11.6 11.2 11.2 |  9.3  8.9  9.5 | 7.2  7.6  8.4
+//  30,000  13.2 12.8 13.8 |  9.7  9.4 10.9 | 7.6  8.0  9.4
+//  40,900  13.9 14.2 18.1 | 11.0 10.7 14.7 | 8.4  8.9 12.8
+// and of 30,000 of many sizes 38.5 41.7 47.4 (a search on most steps).  Beds
+// with many walls gain more (37,000 of a flat bed, FP64, rolling friction, with
+// their coupling: 21.9 and 20.1 us per step).  Hence four while they are three
+// quarters of a wavefront per SIMD, two up to two and a half.  The kernels of a
+// batch take one: they are made for batches that fill the chip.
 static int list_share(int n) {
   constexpr long long kSimds = 1024;
   const long long waves = (2ll * n + kForceBlock - 1) / kForceBlock;  // one lane for each part
-  return 4 * waves <= kSimds ? 4 : (4 * waves <= 5 * kSimds ? 2 : 1);
+  return 16 * waves <= 3 * kSimds ? 4 : (4 * waves <= 5 * kSimds ? 2 : 1);
 }
 
 template <bool ROLL>

@@ -100,7 +100,7 @@ def test_full_lists_shared_by_more_lanes(n_side, precision):
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
 @pytest.mark.parametrize("mu_r", [0.0, 0.1])
-@pytest.mark.parametrize("n_side", [(16, 16, 31), (35, 35, 34)])  # four lanes to a list's part, and one
+@pytest.mark.parametrize("n_side", [(12, 12, 28), (35, 35, 34)])  # four lanes to a list's part, and one
 def test_every_share_of_a_list_has_the_same_bits_each_time(n_side, mu_r, precision):
     wl = _moving_lattice(n_side, mu_r)
     runs = []
@@ -151,7 +151,7 @@ def test_a_part_of_a_list_has_the_same_sum_for_any_number_of_lanes(mu_r, precisi
     k = np.arange(41000)
     rest = np.stack([(1 + k % 36) * 1.3 * d, (1 + k // 36 % 36) * 1.3 * d, top + (1 + k // 1296) * 1.3 * d])
     runs = []
-    for extra in (0, 20000, 41000):
+    for extra in (0, 10000, 41000):
         one = synth.lattice(n_side=(2, 2, 2))
         one.dem, one.fluid = wl.dem, wl.fluid
         one.x = np.concatenate([wl.x, rest[:, :extra]], 1)
