@@ -79,6 +79,9 @@ bool finite_pos(double v) { return isfinite(v) && v > 0.0; }
 // (C = Q diag(lam) Q^T), then V = L^-T Q, so that V^T M V = I and
 // V^T K V = diag(lam).  V is returned row-major with the eigenvectors as
 // columns.  False if M is not positive definite.
+// On a cache line of its own: its short loops took 34 or 44 ms (nodes 41, 41,
+// 161) as the code around it changed.
+__attribute__((noinline, aligned(64)))
 bool gen_eig(int n, const std::vector<double> &M, const std::vector<double> &K, std::vector<double> &V,
              std::vector<double> &lam) {
   const size_t N = (size_t)n;
