@@ -188,3 +188,41 @@ def test_a_batch_of_one_has_the_bits_of_the_bed_alone(n_side, lanes, mu_r, preci
         assert np.array_equal(p, q)
     assert alone.poll()[0] == 0 and other.poll()[0] == 0
     batch.close()
+
+
+@pytest.mark.parametrize("resort_every", [4, 1000])
+@pytest.mark.parametrize("lanes", [1, 2, 4])
+@pytest.mark.parametrize("n_el", [[10, 10, 10], [6, 9, 7]])  # cells of 1.06 d_max; of 1.8, 1.2 and 1.5
+def test_no_partner_is_missed_among_spheres_of_many_sizes(n_el, lanes, resort_every):
+    """Radii from 0.4 to 1.6 mm in a box away from the origin, in fast motion:
+    the contacts at the bed's own positions, found by brute force, before and
+    after broad searches that leave out the cells out of reach."""
+    rng = np.random.default_rng(12)
+    wl = synth.lattice(n_side=(2, 2, 2))
+    lo = np.array([-0.7, 1.3, 20.0])
+    k = np.arange(16 ** 3)
+    x = 1.9e-3 * (np.stack([k % 16, k // 16 % 16, k // 256]) + 0.6) + rng.uniform(-4e-4, 4e-4, (3, k.size))
+    wl.x = x + lo[:, None] + 1.5e-3  # away from the walls
+    wl.radius = rng.uniform(0.4e-3, 1.2e-3, k.size)
+    wl.radius[::40] = 1.6e-3
+    wl.density = np.full(k.size, 2500.0)
+    wl.v, wl.w = rng.normal(0.0, 0.5, x.shape), np.zeros(x.shape)
+    wl.dem["box_lo"], wl.dem["box_hi"] = list(lo), list(lo + 0.0340)
+    wl.dem.update(E=1e4, E_w=1e4)  # the overlaps come apart slowly
+    wl.fluid["n_el"] = n_el
+    gb = gpu_bed(wl, "fp64", lanes=lanes, resort_every=resort_every, skin=5e-5, cell_capacity=64, max_neighbors=64)
+    found = 0
+    for _ in range(12):
+        gb.step(5)
+        assert gb.poll()[0] == 0
+        p = gb.read_state()["x"].cpu().numpy()
+        d = p[:, None, :] - p[:, :, None]
+        rs = wl.radius[:, None] + wl.radius[None, :]
+        touch = rs * rs - (d[0] * d[0] + d[1] * d[1] + d[2] * d[2]) > 0.0
+        i, j, _ = gb.read_contacts()
+        got = np.zeros_like(touch)
+        got[i[j >= 0], j[j >= 0]] = True
+        want = np.triu(touch, 1)
+        assert np.array_equal(got, want)
+        found += int(want.sum())
+    assert found > 12 * 3000
