@@ -887,9 +887,9 @@ __device__ inline int xcd_run_block(int i, int nb, int C) {
 // Wavefronts per SIMD that the force kernels leave registers for.  Four are
 // 128 registers, which holds every FP32 variant and the plain FP64 ones; with
 // rolling friction, or with four lanes over a batch's table, the FP64 kernel
-// needs up to 14 more.  It gets them: held in scratch memory instead they cost time on every
-// step, and a build that did so gave results that differed from run to run (the
-// reason was not found, so the build refuses such a kernel).
+// needs up to 14 more.  It gets them: held in scratch memory instead they cost
+// time on every step, and a build that did so gave results that differed from
+// run to run (the reason was not found, so the build refuses such a kernel).
 template <typename R, bool ROLL, bool BATCH, int L>
 constexpr int force_waves() {
   return sizeof(R) == 8 && (ROLL || (BATCH && L == 4)) ? 3 : 4;
