@@ -190,6 +190,26 @@ def test_a_batch_of_one_has_the_bits_of_the_bed_alone(n_side, lanes, mu_r, preci
     batch.close()
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n", [6144, 6145])
+def test_largest_bed_of_four_lanes_and_the_next(n, precision):
+    """A bed's lanes change from four to two; a batch of one takes one."""
+    wl = _moving_lattice((12, 16, 33), 0.1)
+    wl.x, wl.v, wl.w = wl.x[:, :n].copy(), wl.v[:, :n].copy(), wl.w[:, :n].copy()
+    wl.radius, wl.density = wl.radius[:n].copy(), wl.density[:n].copy()
+    alone, other = (gpu_bed(wl, precision, skin=1e-5) for _ in range(2))
+    batch = cfddem.Batch([other])
+    alone.step(3)
+    batch.step(3)
+    a, b = gpu_state(alone), gpu_state(other)
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
+    for p, q in zip(alone.read_contacts(), other.read_contacts()):
+        assert np.array_equal(p, q)
+    assert alone.poll()[0] == 0 and other.poll()[0] == 0
+    batch.close()
+
+
 @pytest.mark.parametrize("resort_every", [4, 1000])
 @pytest.mark.parametrize("lanes", [1, 2, 4])
 @pytest.mark.parametrize("n_el", [[10, 10, 10], [6, 9, 7]])  # cells of 1.06 d_max; of 1.8, 1.2 and 1.5
